@@ -264,8 +264,8 @@ hlb_status hlb_mass_balance(hlb_ctx *ctx, double *mass, double *residual);
  * returns, to `out`, caller-owned device memory of 2 doubles, asynchronously
  * on the context stream.  It calls no hipMalloc / hipFree and does not
  * synchronise; the non-finite check of hlb_mass_balance is left to the
- * caller.  The reduction's partial sums go to a fixed array of 8,192
- * doubles (64 KiB) in device memory that every GPU the library runs on
+ * caller.  The reduction's partial sums go to a fixed array of 4,096
+ * doubles (32 KiB) in device memory that every GPU the library runs on
  * holds until the process ends; each call overwrites the slots it reads, so
  * nothing is cleared between calls, and any site count is served (larger
  * states stride over the slots).  All calls on one GPU share that array:

@@ -148,6 +148,31 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// flux[slot of this wavefront] += the wavefront's sum of v (see kFluxSlots);
+// all 64 lanes must call it.
+__device__ inline void add_flux(double *flux, double v) {
+  static_assert((kFluxSlots & (kFluxSlots - 1)) == 0, "slot count is a power of two");
+  const double s = wave_sum(v);
+  if ((threadIdx.x & 63) == 0 && s != 0.0)
+    atomicAdd(flux + (((uint32_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) & (kFluxSlots - 1)), s);
+}
+
+// The sum of the partial sums, in the same order wherever it is formed: every
+// thread of a kBlock-thread workgroup calls it; the value is thread 0's.
+__device__ inline double sum_flux(const double *flux, double *red) {
+  double s = 0.0;
+#pragma unroll 4
+  for (int k = threadIdx.x; k < kFluxSlots; k += kBlock) s += flux[k];
+  s = wave_sum(s);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  double b = 0.0;
+  if (threadIdx.x == 0)
+    for (int w = 0; w < kBlock / 64; ++w) b += red[w];
+  return b;
+}
+
 // Per-site outflow of a Windkessel outlet (k < 0: none), gathered while the
 // site's links are processed; a site touching a second such outlet adds that
 // one directly.
@@ -328,6 +353,26 @@ __device__ inline void bulk_offsets_wave(const GatherArgs &a, int64_t p, int64_t
   }
 }
 
+// Porous walls of bulk+wall position p: the reflected values g[i] of its wall
+// links (bit i of `walls`) become (1 - phi) g_i + phi w_i rho0; returns the
+// mass added.  One region after the gathers: a rule inside the gather loop,
+// with its own load of phi, made every later gather wait for the one before.
+template <bool SH, typename C>
+__device__ inline C porous_walls(const GatherArgs &a, int64_t p, uint32_t walls, C (&g)[Q]) {
+  C flux = 0;
+  if (walls) {
+    const C ph = C(a.phi[p]);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      const C nv = g[i] - ph * (g[i] - rest<SH, C>(i, C(a.rho0)));
+      const bool wall = (walls >> i) & 1u;
+      flux += wall ? nv - g[i] : C(0);
+      g[i] = wall ? nv : g[i];
+    }
+  }
+  return flux;
+}
+
 // Pre-collision populations of site p at time t+1, gathered from the
 // post-collision buffer A of time t (stored values s = f - off), with the
 // boundary rules (Sec. 2.3) for links that do not reach a fluid site:
@@ -372,6 +417,7 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
     const uint32_t own = N::voff(pb);
     const uint32_t wall_lo = own - N::D, wall_hi = own + N::D;  // (p, opp(i)) for even / odd i
     const uint32_t jb_wall = ((uint32_t)np << N::S) + N::D;
+    uint32_t walls = 0;
     g[0] = ld(N::at(A, 0, own));
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
@@ -379,16 +425,10 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
       uint32_t vj = N::voff(jb);
       asm("" : "+v"(vj));
       const bool wall = jb >= jb_wall;
-      C v = ld(N::at(A, i, wall ? (opp(i) > i ? wall_hi : wall_lo) : vj));
-      if constexpr (POROUS) {
-        if (wall) {
-          const C nv = v - C(a.phi[p]) * (v - rest<SH, C>(i, C(a.rho0)));
-          flux += nv - v;
-          v = nv;
-        }
-      }
-      g[i] = v;
+      g[i] = ld(N::at(A, i, wall ? (opp(i) > i ? wall_hi : wall_lo) : vj));
+      if constexpr (POROUS) walls |= (uint32_t)wall << i;
     }
+    if constexpr (POROUS) flux = porous_walls<SH>(a, p, walls, g);
   } else if constexpr (!IOLET) {
     // Bulk+wall group: every link, bounce-back included, is one load; the
     // offsets are fetched before the 18 gathers are issued.
@@ -398,6 +438,7 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
     else
       bulk_offsets(a, p, blk, off);
     const int32_t p32 = (int32_t)p;
+    uint32_t walls = 0;
     g[0] = ld(at<NARROW>(A, p32, 0));
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
@@ -405,16 +446,10 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
       // direction opp(i)
       const int32_t j = p32 + off[i - 1];
       const bool wall = (uint32_t)j >= (uint32_t)np;
-      C v = ld(at<NARROW>(A, wall ? p32 : j, wall ? opp(i) : i));
-      if constexpr (POROUS) {
-        if (wall) {
-          const C nv = v - C(a.phi[p]) * (v - rest<SH, C>(i, C(a.rho0)));
-          flux += nv - v;
-          v = nv;
-        }
-      }
-      g[i] = v;
+      g[i] = ld(at<NARROW>(A, wall ? p32 : j, wall ? opp(i) : i));
+      if constexpr (POROUS) walls |= (uint32_t)wall << i;
     }
+    if constexpr (POROUS) flux = porous_walls<SH>(a, p, walls, g);
   } else {
     // density and velocity at time t: moments of the site's own
     // post-collision state (the collision conserves rho and rho u)

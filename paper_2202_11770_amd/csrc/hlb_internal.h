@@ -35,6 +35,15 @@ constexpr int64_t kSegBlock = 256;
 constexpr int kPopTileShift = 12;
 constexpr int64_t kPopTile = int64_t(1) << kPopTileShift;
 
+// The step kernels add each wavefront's boundary mass flux to one of
+// kFluxSlots partial sums (wavefront index mod kFluxSlots): with porous walls
+// nearly every wavefront has a share, and one address takes them one after
+// the other (12 ns each: the FP32 step of a 1.1e6-site tree took 226 us, and
+// takes 54 us with the sums spread and porous_walls() after the gathers).  The sums are folded into DevPtrs::acc[0] before that is read.
+constexpr int kFluxSlots = 4096;
+// Partial sums of the mass reduction (one per workgroup, at most).
+constexpr int64_t kMassPartials = 4096;
+
 struct IoletDev {
   int32_t kind;     // HLB_IOLET_VELOCITY / HLB_IOLET_PRESSURE
   int32_t tab_len;  // >= 1
@@ -78,7 +87,9 @@ struct DevPtrs {
   IoletDev *io = nullptr;           // [n_iolets]
   double *tables = nullptr;         // concatenated per-step iolet tables
   double *phi = nullptr;            // [np] porosity, or null
-  double *acc = nullptr;            // [4] FP64 accumulators: boundary flux since t0, ...
+  double *acc = nullptr;            // [4] FP64 accumulators: boundary flux since t0 up to the last fold, ...
+  double *flux = nullptr;           // [kFluxSlots] boundary flux since the last fold (see kFluxSlots);
+                                    // the tail of the allocation of `partial`
   double *partial = nullptr;        // [partial_len] reduction scratch
   int64_t partial_len = 0;
   double *io_scratch = nullptr;     // [np*19] host-exchange staging (allocated lazily)
@@ -130,6 +141,8 @@ hipError_t launch_macros(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d
 // buffer `pre` := f - w rho0, buffer 1-pre := its collision.
 hipError_t launch_set_state(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, int pre,
                             const double *staging, hipStream_t s);
+// acc[0] += the sum of the partial sums flux[0..kFluxSlots), which are cleared.
+hipError_t launch_fold_flux(double *acc, double *flux, hipStream_t s);
 // p[0..n) := 0 (a kernel, so that no memset node lands in a captured graph).
 hipError_t launch_zero(double *p, int64_t n, hipStream_t s);
 // After the update t -> t+1: Windkessel outlets take their outflow, advance

@@ -70,7 +70,7 @@ constexpr bool kStepLdsRows = sizeof(T) != 2;
 template <typename T, bool POROUS, bool NARROW, int SPT = 1>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T, SPT, NARROW>, 8))) void k_step(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
-    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *acc) {
+    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots) {
   using C = typename Acc<T>::type;
   constexpr bool SH = kShifted<T>;
   const int64_t b = blockIdx.x;
@@ -85,8 +85,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
 #pragma unroll
       for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p, i), g[i]);
     }
-    const double s = wave_sum(double(flux));
-    if ((threadIdx.x & 63) == 0 && s != 0.0) atomicAdd(acc, s);
+    add_flux(flux_slots, double(flux));
     if (a.io_flux) wave_add_grouped(a.io_flux, wkf);
   } else if constexpr (SPT == 1) {
     const int64_t blk = blk0 + block_id(b - nb_io, nb_bulk, xcd_chunk);
@@ -120,10 +119,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
         for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p, i), g[i]);
       }
     }
-    if constexpr (POROUS) {
-      const double s = wave_sum(double(flux));
-      if ((threadIdx.x & 63) == 0 && s != 0.0) atomicAdd(acc, s);
-    }
+    if constexpr (POROUS) add_flux(flux_slots, double(flux));
   } else {
     const int64_t blk = 2 * block_id(b - nb_io, nb_bulk, xcd_chunk);
     const int64_t p = blk * kBlock + threadIdx.x;
@@ -144,10 +140,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
 #pragma unroll
       for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p2, i), h[i]);
     }
-    if constexpr (POROUS) {
-      const double s = wave_sum(double(flux));
-      if ((threadIdx.x & 63) == 0 && s != 0.0) atomicAdd(acc, s);
-    }
+    if constexpr (POROUS) add_flux(flux_slots, double(flux));
   }
 }
 
@@ -158,7 +151,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
 template <typename T, bool POROUS, bool NARROW>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T>, 8))) void k_step_push(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
-    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *acc) {
+    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots) {
   using C = typename Acc<T>::type;
   constexpr bool SH = kShifted<T>;
   const int64_t b = blockIdx.x;
@@ -175,8 +168,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
       collide<SH>(f, omega, C(a.rho0));
       flux = scatter<true, POROUS, SH, NARROW>(B, p, 0, a, f, jx / rho, jy / rho, jz / rho, rho, &wkf);
     }
-    const double s = wave_sum(double(flux));
-    if ((threadIdx.x & 63) == 0 && s != 0.0) atomicAdd(acc, s);
+    add_flux(flux_slots, double(flux));
     if (a.io_flux) wave_add_grouped(a.io_flux, wkf);
   } else {
     const int64_t blk = blk0 + block_id(b - nb_io, nb_bulk, xcd_chunk);
@@ -188,10 +180,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
       collide<SH>(f, omega, C(a.rho0));
       flux = scatter<false, POROUS, SH, NARROW>(B, p, blk, a, f, C(0), C(0), C(0), C(0));
     }
-    if constexpr (POROUS) {
-      const double s = wave_sum(double(flux));
-      if ((threadIdx.x & 63) == 0 && s != 0.0) atomicAdd(acc, s);
-    }
+    if constexpr (POROUS) add_flux(flux_slots, double(flux));
   }
 }
 
@@ -395,6 +384,14 @@ __global__ void k_windkessel(const IoletDev *io, WkParams *wk, double *wk_rho, d
 __global__ void k_set_time(int64_t *p, int64_t v) { *p = v; }
 __global__ void k_add_time(int64_t *p, int64_t k) { *p += k; }
 
+__global__ __launch_bounds__(kBlock) void k_fold_flux(double *acc, double *flux) {
+  __shared__ double red[kBlock / 64];
+  const double s = sum_flux(flux, red);
+  if (threadIdx.x == 0) acc[0] += s;
+#pragma unroll
+  for (int k = threadIdx.x; k < kFluxSlots; k += kBlock) flux[k] = 0.0;
+}
+
 __global__ void k_zero(double *p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0.0;
@@ -432,13 +429,13 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
   do {                                                                                                  \
     if (cfg.scheme == HLB_SCHEME_PUSH)                                                                  \
       k_step_push<T, P, N><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk,          \
-                                                   cfg.xcd_chunk, omega, d.acc);                        \
+                                                   cfg.xcd_chunk, omega, d.flux);                        \
     else if (pair)                                                                                      \
       k_step<T, P, N, 2><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, 0, nb_launch,             \
-                                                 cfg.xcd_chunk, omega, d.acc);                          \
+                                                 cfg.xcd_chunk, omega, d.flux);                          \
     else                                                                                                \
       k_step<T, P, N><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk, cfg.xcd_chunk, \
-                                              omega, d.acc);                                            \
+                                              omega, d.flux);                                            \
   } while (0)
     if (cfg.porous) {
       if (narrow) HLB_STEP(true, kStepNarrow<T>);
@@ -580,6 +577,11 @@ hipError_t launch_set_time(int64_t *p, int64_t v, hipStream_t s) {
 
 hipError_t launch_add_time(int64_t *p, int64_t k, hipStream_t s) {
   k_add_time<<<1, 1, 0, s>>>(p, k);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold_flux(double *acc, double *flux, hipStream_t s) {
+  k_fold_flux<<<1, kBlock, 0, s>>>(acc, flux);
   return hipGetLastError();
 }
 

@@ -52,11 +52,12 @@ __global__ __launch_bounds__(kBlock) void k_mass_partial_na(const T *__restrict_
 }
 
 // out[0] = offset + sum of the partials (the total mass), out[1] = out[0] -
-// m0 - acc[0] (the balance residual).
+// m0 - the boundary flux (the balance residual).
 __global__ __launch_bounds__(kBlock) void k_mass_balance_na(const double *partial, int64_t nparts, double offset,
-                                                            double m0, const double *acc, double *out) {
+                                                            double m0, const double *acc, const double *flux,
+                                                            double *out) {
   __shared__ double red[kBlock / 64];
-  double s = 0.0;
+  double s = 0.0, M = 0.0;
   for (int64_t k = threadIdx.x; k < nparts; k += kBlock) s += partial[1 + k];
   s = wave_sum(s);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
@@ -64,10 +65,11 @@ __global__ __launch_bounds__(kBlock) void k_mass_balance_na(const double *partia
   if (threadIdx.x == 0) {
     double b = 0.0;
     for (int w = 0; w < kBlock / 64; ++w) b += red[w];
-    const double M = offset + b;
+    M = offset + b;
     out[0] = M;
-    out[1] = M - m0 - acc[0];
   }
+  const double f = sum_flux(flux, red);
+  if (threadIdx.x == 0) out[1] = M - m0 - (acc[0] + f);
 }
 
 template <typename T>
@@ -76,7 +78,7 @@ hipError_t mass_na(const Layout &L, const DevPtrs &d, int src, double offset, do
   int64_t nb = (L.np + kBlock - 1) / kBlock;
   if (nb > kNoAllocPartials) nb = kNoAllocPartials;
   k_mass_partial_na<T><<<(unsigned)nb, kBlock, 0, s>>>(static_cast<const T *>(d.f[src]), d.order, L.np, scr);
-  k_mass_balance_na<<<1, kBlock, 0, s>>>(scr, nb, offset, m0, d.acc, out);
+  k_mass_balance_na<<<1, kBlock, 0, s>>>(scr, nb, offset, m0, d.acc, d.flux, out);
   return hipGetLastError();
 }
 

@@ -153,7 +153,7 @@ struct TimedStep {
 bool same_launch(const DevPtrs &a, const DevPtrs &b) {
   return a.f[0] == b.f[0] && a.f[1] == b.f[1] && a.seg_off == b.seg_off && a.seg_base == b.seg_base &&
          a.seg_delta == b.seg_delta && a.nbr_io == b.nbr_io && a.order == b.order && a.corr == b.corr &&
-         a.io == b.io && a.tables == b.tables && a.phi == b.phi && a.acc == b.acc && a.wk_rho == b.wk_rho &&
+         a.io == b.io && a.tables == b.tables && a.phi == b.phi && a.acc == b.acc && a.flux == b.flux && a.wk_rho == b.wk_rho &&
          a.io_flux == b.io_flux && a.wk == b.wk;
 }
 bool same_launch(const LaunchCfg &a, const LaunchCfg &b) {
@@ -398,6 +398,7 @@ hlb_status compute_mass(hlb_ctx *c, double *sum_g) {
 
 hlb_status reset_balance(hlb_ctx *c) {
   HIP_TRY(launch_zero(c->d.acc, 4, c->stream));
+  HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
   double s = 0;
   hlb_status st = compute_mass(c, &s);
   if (st) return st;
@@ -782,10 +783,10 @@ static hlb_status create_impl(int64_t n, const int32_t *coords, const uint8_t *t
     return fail(HLB_EDEVICE, "hipGetSymbolAddress of the reduction scratch: %s", hipGetErrorString(he));
   }
   const size_t fb = (size_t)Q * np * storage_bytes(opt.storage);
-  const int64_t partial_len = 1 + 8192;
+  const int64_t partial_len = 1 + kMassPartials;
   const size_t need = 2 * fb + pull_io.size() * sizeof(int32_t) + seg_off.size() * sizeof(int32_t) +
                       seg_base.size() * sizeof(int32_t) + seg_delta.size() + np * sizeof(int32_t) +
-                      corr.size() * sizeof(double) + partial_len * sizeof(double);
+                      corr.size() * sizeof(double) + (partial_len + kFluxSlots) * sizeof(double);
   if (c->max_bytes > 0 && (int64_t)need > c->max_bytes) {
     delete c;
     return fail(HLB_ENOMEM, "needs %zu device bytes, budget is %lld", need, (long long)opt.max_device_bytes);
@@ -821,8 +822,9 @@ static hlb_status create_impl(int64_t n, const int32_t *coords, const uint8_t *t
   c->d.corr = static_cast<double *>(p);
   if ((st = dev_alloc(c, &p, 4 * sizeof(double)))) return bail(st);
   c->d.acc = static_cast<double *>(p);
-  if ((st = dev_alloc(c, &p, partial_len * sizeof(double)))) return bail(st);
+  if ((st = dev_alloc(c, &p, (partial_len + kFluxSlots) * sizeof(double)))) return bail(st);
   c->d.partial = static_cast<double *>(p);
+  c->d.flux = c->d.partial + partial_len;
   c->d.partial_len = partial_len;
   auto cp = [&](void *dst, const void *src, size_t bytes) -> hlb_status {
     hipError_t e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
@@ -1478,6 +1480,7 @@ hlb_status hlb_mass_balance(hlb_ctx *c, double *mass, double *residual) {
   if (hlb_status st = check_ctx(c)) return st;
   if (hlb_status st = bind(c)) return st;
   double s = 0.0, flux = 0.0;
+  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
   if (hlb_status st = compute_mass(c, &s)) return st;
   HIP_TRY(hipMemcpy(&flux, c->d.acc, sizeof(double), hipMemcpyDeviceToHost));
   const double M = mass_offset(c) + s;
@@ -1599,6 +1602,7 @@ hlb_status hlb_snapshot_save(hlb_ctx *c, int32_t slot) {
   auto &s = c->snaps[slot];
   HIP_TRY(hipMemcpyAsync(s.f[0], c->d.f[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(s.f[1], c->d.f[1], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
   HIP_TRY(hipMemcpyAsync(s.acc, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   s.t = c->t; s.t0 = c->t0; s.m0 = c->m0; s.cur = c->cur; s.direct = c->direct; s.valid = true;
   return HLB_OK;
@@ -1613,6 +1617,7 @@ hlb_status hlb_snapshot_restore(hlb_ctx *c, int32_t slot) {
   HIP_TRY(hipMemcpyAsync(c->d.f[0], s.f[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.f[1], s.f[1], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.acc, s.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
   c->t = s.t; c->t0 = s.t0; c->m0 = s.m0; c->cur = s.cur; c->direct = s.direct;
   return HLB_OK;
 }
@@ -1643,6 +1648,7 @@ hlb_status hlb_state_save(hlb_ctx *c, void *buf) {
   h.n_sites = c->L.n_sites; h.np = c->L.np; h.t = c->t; h.t0 = c->t0;
   h.storage = c->cfg.storage; h.cur = c->cur; h.direct = c->direct ? 1 : 0; h.m0 = c->m0;
   h.scheme = c->cfg.scheme;
+  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
   HIP_TRY(hipMemcpyAsync(h.acc, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   char *b = static_cast<char *>(buf);
   HIP_TRY(hipMemcpyAsync(b + sizeof(h), c->d.f[0], buf_bytes(c), hipMemcpyDeviceToHost, c->stream));
@@ -1665,6 +1671,7 @@ hlb_status hlb_state_load(hlb_ctx *c, const void *buf) {
   HIP_TRY(hipMemcpyAsync(c->d.f[0], b + sizeof(h), buf_bytes(c), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.f[1], b + sizeof(h) + buf_bytes(c), buf_bytes(c), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.acc, h.acc, 4 * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->t = h.t; c->t0 = h.t0; c->m0 = h.m0; c->cur = h.cur; c->direct = h.direct != 0;
   return HLB_OK;
@@ -1915,6 +1922,7 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
   const int cur0 = c->cur;
   const bool direct0 = c->direct;
   const int64_t t_start = c->t;
+  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
   HIP_TRY(hipMemcpyAsync(c->adj.J + 1, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->adj_slots[n_snap], c->d.f[1 - cur0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(launch_zero(c->adj.mu, (int64_t)Q * np, c->stream));
@@ -1943,6 +1951,7 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
       e = hipMemcpyAsync(c->d.f[1 - cur0], c->adj_slots[n_snap], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream);
     if (e == hipSuccess)
       e = hipMemcpyAsync(c->d.acc, c->adj.J + 1, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
+    if (e == hipSuccess) e = launch_zero(c->d.flux, kFluxSlots, c->stream);
     if (e != hipSuccess) st = fail(HLB_EDEVICE, "restoring the state: %s", hipGetErrorString(e));
     if (!st) st = R.wk_state(0, false);
   }
