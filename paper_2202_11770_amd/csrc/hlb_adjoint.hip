@@ -42,12 +42,6 @@ struct AdjArgs {
   const double *wq;
 };
 
-// The value iolet k applies in the update a.t -> a.t+1: a Windkessel
-// outlet's density from its model state, else the table value.
-__device__ inline double iolet_value(const GatherArgs &a, const IoletDev &K, int k) {
-  return K.wk ? a.wk_rho[2 * k + (a.t & 1)] : a.tables[K.tab_off + a.t % K.tab_len];
-}
-
 // The wavefront's share s of the objective, added to its partial-sum slot
 // (one atomic per wavefront, spread over kAdjJSlots addresses); lane 0 adds.
 __device__ inline void add_objective(double *J, double s) {
@@ -352,7 +346,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
         if (!(iol & (1u << (i - 1)))) continue;
         const int k = -a.nbr_io[(int64_t)(i - 1) * a.nio + (p - a.io_begin)] - 2;
         const IoletDev K = a.io[k];
-        const double val = iolet_value(a, K, k);
+        const double val = iolet_value(a, K, k, a.t);
         const double wk = A.wq[k];
         const double wo = flux ? A.w[k] : 0.0;
         double coef, out;  // d(filled value)/d(table value); outflow of the link
@@ -454,7 +448,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
       const IoletDev K = a.io[-c - 2];
       if (K.kind != HLB_IOLET_PRESSURE) continue;
       const int o = opp(i);  // incoming population = f^eq_o(rho_k, (u.n) n)
-      const double rk = iolet_value(a, K, -c - 2);
+      const double rk = iolet_value(a, K, -c - 2, a.t);
       const double un = ux * K.n[0] + uy * K.n[1] + uz * K.n[2];
       const double gx = un * K.n[0], gy = un * K.n[1], gz = un * K.n[2];
       const double cu = cx(o) * gx + cy(o) * gy + cz(o) * gz;

@@ -353,6 +353,16 @@ __device__ inline void bulk_offsets_wave(const GatherArgs &a, int64_t p, int64_t
   }
 }
 
+// The value iolet k applies in the update t -> t+1: a Windkessel outlet's
+// density from its model state, else its table at t mod len (the 64-bit
+// division costs about a hundred instructions; times and lengths below 2^32
+// take the 32-bit one).
+__device__ inline double iolet_value(const GatherArgs &a, const IoletDev &K, int k, int64_t t) {
+  if (K.wk) return a.wk_rho[2 * k + (t & 1)];
+  const int64_t s = ((uint64_t)t >> 32) ? t % K.tab_len : (int64_t)((uint32_t)t % (uint32_t)K.tab_len);
+  return a.tables[K.tab_off + s];
+}
+
 // Porous walls of bulk+wall position p: the reflected values g[i] of its wall
 // links (bit i of `walls`) become (1 - phi) g_i + phi w_i rho0; returns the
 // mass added.  One region after the gathers: a rule inside the gather loop,
@@ -369,6 +379,136 @@ __device__ inline C porous_walls(const GatherArgs &a, int64_t p, uint32_t walls,
       flux += wall ? nv - g[i] : C(0);
       g[i] = wall ? nv : g[i];
     }
+  }
+  return flux;
+}
+
+// The link codes of iolet position io_begin + q: per direction one scalar base
+// and a 32-bit lane offset.
+__device__ inline void load_codes(const GatherArgs &a, uint32_t q, int32_t (&code)[Q]) {
+  const uint32_t off = q * 4u;
+#pragma unroll
+  for (int i = 1; i < Q; ++i)
+    code[i] = *reinterpret_cast<const int32_t *>(reinterpret_cast<const char *>(a.nbr_io + (int64_t)(i - 1) * a.nio) + off);
+}
+
+// The next iolet of a site in ascending order (link codes descend from -2;
+// `done`: the last one's code, HLB_LINK_WALL at first): its code, the links
+// that cross it (bit i) and whether another one follows.
+constexpr int kCorrBatch = 9;  // Ladd coefficients in flight (see gather_iolet)
+static_assert((Q - 1) % kCorrBatch == 0, "whole batches");
+struct NextIolet {
+  int32_t code;
+  uint32_t links = 0;
+  bool more = false;
+  __device__ NextIolet(const int32_t (&c)[Q], int32_t done) : code(INT32_MIN) {
+#pragma unroll
+    for (int i = 1; i < Q; ++i)
+      if (c[i] < done && c[i] > code) code = c[i];
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+      links |= (uint32_t)(c[i] == code) << i;
+      more |= c[i] < code;
+    }
+  }
+};
+
+// gather() for a site of the iolet groups, latency first: these few sites
+// are the longest chain of a step, so every load is issued as soon as its
+// address is known -- the 18 link codes and the site's own 19 values, then
+// the 18 sources (of a link that leaves the fluid: the site's own reflected
+// slot), then once per iolet the site touches (one, mostly) its record, and
+// with the record its value and the Ladd coefficients.  The links of one
+// iolet are then filled together from registers.  Per link, with a load of
+// code, source, record, value and coefficient one after the other, the step
+// of the 203,352-site tree with Windkessel outlets took 33 us in FP64 and 29
+// in FP32; so it takes 20.6 and 14.8 us (event time).
+// Its registers decide its speed: within the 80 (FP32, FP16) or 128 (FP64) of
+// the step kernel it has to run without scratch memory.  The barriers for the
+// scheduler, the coefficients in two batches and the addresses formed where
+// they are used see to that (with 56-140 bytes of scratch the FP32 step of the
+// 125,400-site vessel took 13.0 us instead of 8.7, with all coefficients in one
+// batch 16).
+template <bool POROUS, bool SH, bool NARROW, typename T, typename C>
+__device__ inline C gather_iolet(const T *__restrict__ A, int64_t p, const GatherArgs &a, C (&g)[Q], WkFlux *wkf) {
+  const int32_t p32 = (int32_t)p;
+  const uint32_t q = (uint32_t)(p - a.io_begin);  // below 2^30
+  int32_t code[Q];
+  load_codes(a, q, code);
+  // density and velocity at time t: moments of the site's own
+  // post-collision state (the collision conserves rho and rho u)
+  C rho, ux, uy, uz;
+  {
+    C own[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) own[i] = ld(at<NARROW>(A, p32, i));
+    C dr;
+    moments<SH>(own, C(a.rho0), dr, rho, ux, uy, uz);
+    ux = ux / rho;
+    uy = uy / rho;
+    uz = uz / rho;
+    g[0] = own[0];
+  }
+  // own is consumed before the sources are fetched (it arrived with the codes)
+  asm volatile("" : "+v"(rho), "+v"(ux), "+v"(uy), "+v"(uz));
+  __builtin_amdgcn_sched_barrier(0);
+  uint32_t walls = 0;
+#pragma unroll
+  for (int i = 1; i < Q; ++i) {
+    const bool fluid = code[i] >= 0;
+    g[i] = ld(at<NARROW>(A, fluid ? code[i] : p32, fluid ? i : opp(i)));
+    if (i % 6 == 0) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (POROUS) walls |= (uint32_t)(code[i] == HLB_LINK_WALL) << i;
+  }
+  NextIolet io(code, HLB_LINK_WALL);
+  C flux = 0;
+  if constexpr (POROUS) flux = porous_walls<SH>(a, p, walls, g);
+  const int64_t t = step_time(a);
+  while (io.links) {
+    // the addresses of this turn are formed in it (hoisted out of the loop
+    // they would hold 70 registers)
+    uint32_t ql = q;
+    asm volatile("" : "+v"(ql));
+    const int k = -io.code - 2;
+    const IoletDev K = a.io[k];
+    const double val = iolet_value(a, K, k, t);
+    double out = 0.0;  // the links' outflow, in FP64 as the sum it goes to
+    if (K.kind == HLB_IOLET_VELOCITY) {
+      // the Ladd coefficients hold rho0; the local-density rule rescales them
+      const double scale = a.ladd_local ? double(rho) / a.rho0 : 1.0;
+#pragma unroll
+      for (int j = 1; j < Q; j += kCorrBatch) {
+        double corr[kCorrBatch];
+#pragma unroll
+        for (int i = 0; i < kCorrBatch; ++i) corr[i] = a.corr[(int64_t)(j + i - 1) * a.nio + ql];
+#pragma unroll
+        for (int i = j; i < j + kCorrBatch; ++i) {
+          const bool mine = (io.links >> i) & 1u;
+          const C v = g[i] + C(corr[i - j] * val * scale);
+          flux += mine ? v - g[i] : C(0);
+          out += mine ? double(g[i] - v) : 0.0;
+          g[i] = mine ? v : g[i];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      const C un = ux * C(K.n[0]) + uy * C(K.n[1]) + uz * C(K.n[2]);
+      const C gx = un * C(K.n[0]), gy = un * C(K.n[1]), gz = un * C(K.n[2]);
+      const C uu = C(1.5) * (gx * gx + gy * gy + gz * gz);
+#pragma unroll
+      for (int i = 1; i < Q; ++i) {
+        const bool mine = (io.links >> i) & 1u;
+        const C v = s_eq<SH>(i, C(val - a.rho0), C(val), gx, gy, gz, uu);
+        flux += mine ? v - g[i] : C(0);
+        out += mine ? double(g[i] - v) : 0.0;
+        g[i] = mine ? v : g[i];
+      }
+    }
+    if (K.wk && a.io_flux) wkf->add(a.io_flux, k, out);
+    if (!io.more) break;
+    int32_t again[Q];
+    load_codes(a, ql, again);
+    io = NextIolet(again, io.code);
   }
   return flux;
 }
@@ -451,58 +591,7 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
     }
     if constexpr (POROUS) flux = porous_walls<SH>(a, p, walls, g);
   } else {
-    // density and velocity at time t: moments of the site's own
-    // post-collision state (the collision conserves rho and rho u)
-    C ux, uy, uz, rho_x;
-    {
-      C own[Q];
-#pragma unroll
-      for (int i = 0; i < Q; ++i) own[i] = ld(at<NARROW>(A, (int32_t)p, i));
-      C dr, jx, jy, jz;
-      moments<SH>(own, C(a.rho0), dr, rho_x, jx, jy, jz);
-      ux = jx / rho_x;
-      uy = jy / rho_x;
-      uz = jz / rho_x;
-    }
-    // the Ladd coefficients hold rho0; the local-density rule rescales them
-    const double ladd_scale = a.ladd_local ? double(rho_x) / a.rho0 : 1.0;
-    // The reflected values are read again below (cache hits) instead of
-    // being kept live with the 19 gathered ones: the empty asm hides that
-    // q == p, so the compiler cannot merge those reads with the ones above
-    // and keep 19 more registers for them.
-    const int64_t t = step_time(a);
-    int32_t q = (int32_t)p;
-    asm volatile("" : "+v"(q));
-    g[0] = ld(at<NARROW>(A, q, 0));
-#pragma unroll
-    for (int i = 1; i < Q; ++i) {
-      const int32_t code = a.nbr_io[(int64_t)(i - 1) * a.nio + (p - a.io_begin)];
-      if (code >= 0) {
-        g[i] = ld(at<NARROW>(A, code, i));
-        continue;
-      }
-      const C back = ld(at<NARROW>(A, q, opp(i)));
-      C v;
-      if (code == HLB_LINK_WALL) {
-        v = back;
-        if constexpr (POROUS) v = back - C(a.phi[p]) * (back - rest<SH, C>(i, C(a.rho0)));
-      } else {
-        const int k = -code - 2;
-        const IoletDev K = a.io[k];
-        const double val = K.wk ? a.wk_rho[2 * k + (t & 1)] : a.tables[K.tab_off + t % K.tab_len];
-        if (K.kind == HLB_IOLET_VELOCITY) {
-          v = back + C(a.corr[(int64_t)(i - 1) * a.nio + (p - a.io_begin)] * val * ladd_scale);
-        } else {
-          const C un = ux * C(K.n[0]) + uy * C(K.n[1]) + uz * C(K.n[2]);
-          const C gx = un * C(K.n[0]), gy = un * C(K.n[1]), gz = un * C(K.n[2]);
-          const C uu = C(1.5) * (gx * gx + gy * gy + gz * gz);
-          v = s_eq<SH>(i, C(val - a.rho0), C(val), gx, gy, gz, uu);
-        }
-        if (K.wk && a.io_flux) wkf->add(a.io_flux, k, double(back - v));
-      }
-      flux += v - back;
-      g[i] = v;
-    }
+    flux = gather_iolet<POROUS, SH, NARROW>(A, p, a, g, wkf);
   }
   return flux;
 }
@@ -609,7 +698,7 @@ __device__ inline C scatter(T *__restrict__ B, int64_t p, int64_t blk, const Gat
       } else {
         const int k = -code - 2;
         const IoletDev K = a.io[k];
-        const double val = K.wk ? a.wk_rho[2 * k + (t & 1)] : a.tables[K.tab_off + t % K.tab_len];
+        const double val = iolet_value(a, K, k, t);
         if (K.kind == HLB_IOLET_VELOCITY) {
           v = back + C(a.corr[(int64_t)(i - 1) * a.nio + (p - a.io_begin)] * val * ladd_scale);
         } else {

@@ -78,12 +78,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
   if (b < nb_io) {
     const int64_t p = a.io_begin + b * kBlock + threadIdx.x;
     WkFlux wkf;
-    if (p < a.np && order[p] >= 0) {
-      C g[Q];
-      flux = gather<true, POROUS, SH, NARROW>(A, p, 0, a, g, &wkf);
+    // a padding position (wall links only, zero values) goes through the
+    // gather too, so that it need not wait for its order entry, and stores
+    // nothing
+    const int32_t id = order[p];
+    C g[Q];
+    flux = gather_iolet<POROUS, SH, NARROW>(A, p, a, g, &wkf);
+    if (id >= 0) {
       collide<SH>(g, omega, C(a.rho0));
+      // store addresses formed here, not shared with the loads of the site's
+      // own slots (they would be kept, and spilled, across the whole path)
+      int32_t ps = (int32_t)p;
+      asm volatile("" : "+v"(ps));
 #pragma unroll
-      for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p, i), g[i]);
+      for (int i = 0; i < Q; ++i) st(at<NARROW>(B, ps, i), g[i]);
+    } else {
+      flux = 0;
     }
     add_flux(flux_slots, double(flux));
     if (a.io_flux) wave_add_grouped(a.io_flux, wkf);
@@ -411,7 +421,8 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
   const int64_t nb_all = (n0 + kBlock - 1) / kBlock;
   // part 0: the whole step; 1: iolet groups + the edge blocks of the
   // bulk+wall group; 2: its remaining blocks
-  const int64_t nb_io = part == 2 ? 0 : (L.nio + kBlock - 1) / kBlock;
+  // the iolet groups' blocks, without the padding and the ghosts behind them
+  const int64_t nb_io = part == 2 ? 0 : (L.gbeg[kGroups] - L.io_begin) / kBlock;
   const int64_t blk0 = part == 2 ? L.edge_blocks : 0;
   const int64_t nb_bulk = part == 0 ? nb_all : (part == 1 ? L.edge_blocks : nb_all - L.edge_blocks);
   // two bulk+wall sites per thread: full pull steps only
