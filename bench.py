@@ -324,13 +324,9 @@ def run_adjoint(g, tables, tau, n=40, n_snap=10):
     half of n steps; also timed with every step inside the window and with
     none, and the mean for the differentiation protocol's window, the last
     sixth of the steps): the reverse step's kernels timed with HIP events
-    and set against their algorithmic bytes per site:
-      k_adj_collide: gather of s (19 x 8 + the pull table), mu read, nu
-                     written (19 x 8 each), porosity derivative read and
-                     written (16), order (4);
-      k_adj_stream:  order (4), the pull table again (its entry opp(i) names
-                     the site that pulled population i), nu gathered and mu
-                     written (19 x 8 each)."""
+    and set against the algorithmic bytes per site of k_adj_step: gather of s
+    and of the next step's nu (19 x 8 each), nu written (19 x 8), the pull
+    table."""
     from paper_2202_11770_amd import hlb
     sim = hlb.Simulation.create(g, tau, tables=tables, adjoint=True)
     info = sim.info()
@@ -343,8 +339,7 @@ def run_adjoint(g, tables, tau, n=40, n_snap=10):
         return J, fw, wall, hlb.hlb_stats(sim.ctx)["adj_ms"]
 
     J, fw, wall, adj_ms = timed(n // 2, n)
-    # reverse steps inside the objective window (the boundary kernel also
-    # takes every wall site) and outside it (iolet sites only)
+    # reverse steps inside the objective window and outside it
     in_ms = timed(0, n)[3]
     out_ms = timed(n, n)[3]
     # the forward step kernel in the same context (its site order)
@@ -352,7 +347,7 @@ def run_adjoint(g, tables, tau, n=40, n_snap=10):
     sim.step(20)
     fwd_ms = hlb.hlb_stats(sim.ctx)["kernel_ms"]
     sim.close()
-    bps = 5 * 19 * 8 + 2 * info["table_bytes_per_site"] + 16 + 4 + 4
+    bps = 3 * 19 * 8 + info["table_bytes_per_site"]
     gbs = lambda ms: bps * info["n_sites"] / (ms * 1e-3) / 1e9
     c4_ms = (500 * in_ms + 2500 * out_ms) / 3000  # the protocol's window: the last 500 of 3000 steps
     return {"steps": n, "snapshots": n_snap, "window": [n // 2, n], "forward_steps": fw, "wall_s": round(wall, 3),

@@ -300,7 +300,7 @@ void free_all(hlb_ctx *c) {
   c->flag_dev = nullptr;
   for (auto &s : c->snaps) { F(s.f[0]); F(s.f[1]); F(s.acc); }
   c->snaps.clear();
-  F(c->adj.mu); F(c->adj.nu); F(c->adj.J); F(c->adj.dA); F(c->adj.dphi); F(c->adj.w); F(c->adj.blist);
+  F(c->adj.nu[0]); F(c->adj.nu[1]); F(c->adj.J); F(c->adj.dA); F(c->adj.dphi); F(c->adj.w);
   for (void *q : c->adj_slots) F(q);
   c->adj_slots.clear();
   F(c->adj_wk_slots);
@@ -723,18 +723,7 @@ static hlb_status create_impl(int64_t n, const int32_t *coords, const uint8_t *t
   for (int64_t p = 0; p < n0; ++p) seg_delta[p] = (uint8_t)(segid[p] - segid[(p / kSegBlock) * kSegBlock]);
   segid.clear();
   segid.shrink_to_fit();
-  // the adjoint's transposed gather reads the pull tables; it only needs the
-  // list of the sites with wall or iolet links (boundary terms)
-  c->adj_on = opt.adjoint != 0;
-  std::vector<int32_t> blist;
-  if (c->adj_on)
-    for (int64_t p = 0; p < np; ++p) {
-      const int32_t x = c->order_host[p];
-      if (x < 0) continue;
-      bool any = false;
-      for (int i = 1; i < Q && !any; ++i) any = nbr[Q * (int64_t)x + i] < 0;
-      if (any) blist.push_back((int32_t)p);
-    }
+  c->adj_on = opt.adjoint != 0;  // the adjoint's transposed gather reads the pull tables
   // ---- Ladd coefficients 6 w_i rho0 (c_i . v_k) W_k(x - c_i/2) of velocity-iolet links ----
   std::vector<double> corr((size_t)18 * L.nio, 0.0);
 #pragma omp parallel for schedule(static)
@@ -836,14 +825,6 @@ static hlb_status create_impl(int64_t n, const int32_t *coords, const uint8_t *t
   if ((st = cp(c->d.seg_base, seg_base.data(), seg_base.size() * sizeof(int32_t)))) return bail(st);
   if ((st = cp(c->d.seg_delta, seg_delta.data(), seg_delta.size()))) return bail(st);
   if ((st = cp(c->d.order, c->order_host.data(), np * sizeof(int32_t)))) return bail(st);
-  if (!blist.empty()) {
-    if ((st = dev_alloc(c, &p, blist.size() * sizeof(int32_t)))) return bail(st);
-    c->adj.blist = static_cast<int32_t *>(p);
-    c->adj.n_blist = (int64_t)blist.size();
-    c->adj.n_blist_wall =
-        (int64_t)(std::lower_bound(blist.begin(), blist.end(), (int32_t)L.io_begin) - blist.begin());
-    if ((st = cp(c->adj.blist, blist.data(), blist.size() * sizeof(int32_t)))) return bail(st);
-  }
   if (!corr.empty() && (st = cp(c->d.corr, corr.data(), corr.size() * sizeof(double)))) return bail(st);
   if ((st = upload_tables(c))) return bail(st);
   if ((st = hlb_init_equilibrium(c, nullptr, nullptr, 0))) return bail(st);
@@ -1828,6 +1809,7 @@ struct Revolve {
     }
     HIP_TRY(launch_adjoint_step(c->cfg, c->L, reading_slot(), c->cur, t, c->adj, in_window, n, t - 1 - t0,
                                 c->stream));
+    c->adj.cur = 1 - c->adj.cur;
     if (e1) HIP_TRY(hipEventRecord(e1, c->stream));
     return HLB_OK;
   }
@@ -1873,11 +1855,11 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
   if (hlb_status st = bind(c)) return st;
   const int64_t np = c->L.np, nio = (int64_t)c->iolets.size();
   void *p = nullptr;
-  if (!c->adj.mu) {
+  if (!c->adj.nu[0]) {
     if (hlb_status st = dev_alloc(c, &p, (size_t)Q * np * sizeof(double))) return st;
-    c->adj.mu = static_cast<double *>(p);
+    c->adj.nu[0] = static_cast<double *>(p);
     if (hlb_status st = dev_alloc(c, &p, (size_t)Q * np * sizeof(double))) return st;
-    c->adj.nu = static_cast<double *>(p);
+    c->adj.nu[1] = static_cast<double *>(p);
     if (hlb_status st = dev_alloc(c, &p, (size_t)np * sizeof(double))) return st;
     c->adj.dphi = static_cast<double *>(p);
     // [0] the objective; [1, 5) the caller's flux accumulators while the sweep runs
@@ -1925,7 +1907,12 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
   HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
   HIP_TRY(hipMemcpyAsync(c->adj.J + 1, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->adj_slots[n_snap], c->d.f[1 - cur0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(launch_zero(c->adj.mu, (int64_t)Q * np, c->stream));
+  // nu past the last step, and mu there in the iolet groups' slots of the
+  // other buffer (whole tiles from the one where the groups begin)
+  const int64_t io_tile = c->L.io_begin / kPopTile * kPopTile;
+  c->adj.cur = 0;
+  HIP_TRY(launch_zero(c->adj.nu[0], (int64_t)Q * np, c->stream));
+  HIP_TRY(launch_zero(c->adj.nu[1] + Q * io_tile, Q * (np - io_tile), c->stream));
   HIP_TRY(launch_zero(c->adj.dphi, np, c->stream));
   HIP_TRY(launch_zero(c->adj.J + 8, kAdjJSlots, c->stream));
   HIP_TRY(launch_zero(c->adj.dA, std::max<int64_t>(1, nio * n), c->stream));
