@@ -80,21 +80,6 @@ __device__ inline void eq_transpose(const double (&w)[Q], double rho, double ux,
   }
 }
 
-// The segment rows of a bulk+wall block staged in LDS, as in the forward
-// step kernel (one coalesced pass instead of five row loads per lane, and
-// per link-mask / gather pass): every thread of the block must call it.
-// Returns p's row.
-__device__ inline const int4 *stage_rows(const AdjArgs &A, int64_t blk, int64_t p, int4 *lrows) {
-  const GatherArgs &a = A.a;
-  const int32_t k_row = p < A.n0 ? (int32_t)ld_stream(a.seg_delta + p) : 0;
-  const int64_t last = blk * kBlock + kBlock - 1 < A.n0 ? blk * kBlock + kBlock - 1 : A.n0 - 1;
-  const int32_t n4 = ((int32_t)a.seg_delta[last] + 1) * (kSegRow / 4);
-  const int4 *rows = reinterpret_cast<const int4 *>(a.seg_off + (int64_t)a.seg_base[blk] * kSegRow);
-  for (int k = threadIdx.x; k < n4; k += kBlock) lrows[k] = rows[k];
-  __syncthreads();
-  return lrows + (kSegRow / 4) * k_row;
-}
-
 // Outflow weights of the reverse step of the update s -> s+1 (s = step):
 // the objective's weight inside its window, plus, for a Windkessel outlet,
 // dJ/dQ_k(s) from the adjoint of its model:
@@ -191,7 +176,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAdjWave
   const int64_t p = blk * kBlock + threadIdx.x;
   // bulk+wall blocks (block-uniform): the segment rows through LDS
   __shared__ int4 lrows[kSegBlock * (kSegRow / 4)];
-  const int4 *lrow = bulk ? stage_rows(A, blk, p, lrows) : nullptr;
+  const int4 *lrow = bulk ? stage_rows<false>(a, blk, p, A.n0, lrows) : nullptr;
   double jsum = 0.0;
   if (!bulk || p < A.n0) {
     const int32_t p32 = (int32_t)p;

@@ -297,9 +297,36 @@ __device__ inline void bulk_offsets(const GatherArgs &a, int64_t p, int64_t blk,
   off[17] = r[4].y;
 }
 
-// bulk_offsets from p's row staged in LDS (the rows of p's block are the
-// segments seg_base[blk] .. seg_base[blk] + seg_delta of its last position;
-// p's row is entry seg_delta[p]).
+// The segment rows of bulk+wall block blk staged in LDS (lrows: kSegBlock
+// rows): one coalesced pass over the block's segments (typically 20-50)
+// instead of five row loads per lane.  Every thread of the block calls it;
+// returns p's row (any of them past the group's end n0).
+// SHORT: the rows' extent comes from two blocks' first segments, one scalar
+// load, with p's row index fetched beside it; else from the last position's
+// index, behind p's.  The short chain of loads takes FP16, whose blocks are the
+// shortest, from 140.2 to 138.3 us on the 7.8e6-site tree (against its rows
+// loaded per wavefront); FP64 and FP32 run 0.4% and 1.3% slower with it on the
+// 2.0e7-site tree (1036 to 1040 us, 554 to 562), and as fast on small ones.
+template <bool SHORT>
+__device__ inline const int4 *stage_rows(const GatherArgs &a, int64_t blk, int64_t p, int64_t n0, int4 *lrows) {
+  int32_t k_row, n4;
+  const int32_t first = a.seg_base[blk];
+  if constexpr (SHORT) {
+    k_row = (int32_t)ld_stream(a.seg_delta + (p < n0 ? p : n0 - 1));
+    n4 = (a.seg_base[blk + 1] - first + 1) * (kSegRow / 4);  // the next block may share the last segment
+    if (n4 > (int32_t)kSegBlock * (kSegRow / 4)) n4 = (int32_t)kSegBlock * (kSegRow / 4);
+  } else {
+    k_row = p < n0 ? (int32_t)ld_stream(a.seg_delta + p) : 0;
+    const int64_t last = blk * kBlock + kBlock - 1 < n0 ? blk * kBlock + kBlock - 1 : n0 - 1;
+    n4 = ((int32_t)a.seg_delta[last] + 1) * (kSegRow / 4);
+  }
+  const int4 *rows = reinterpret_cast<const int4 *>(a.seg_off + (int64_t)first * kSegRow);
+  for (int k = threadIdx.x; k < n4; k += kBlock) lrows[k] = rows[k];
+  __syncthreads();
+  return lrows + (kSegRow / 4) * k_row;
+}
+
+// bulk_offsets from p's row staged in LDS.
 __device__ inline void lds_offsets(const int4 *row, int32_t (&off)[Q - 1]) {
   int4 r[5];
 #pragma unroll
@@ -313,44 +340,6 @@ __device__ inline void lds_offsets(const int4 *row, int32_t (&off)[Q - 1]) {
   }
   off[16] = r[4].x;
   off[17] = r[4].y;
-}
-
-// bulk_offsets for a whole wavefront (all 64 lanes active or not, each with
-// its own p in ascending order): where the lanes' segments are at most two
-// consecutive ones, both rows are read with scalar loads, which bypass the
-// vector memory path's address processing, and each lane selects its row;
-// otherwise every lane loads its own row.  The segment table carries one
-// padding row, so that row first+1 exists.
-__device__ inline void bulk_offsets_wave(const GatherArgs &a, int64_t p, int64_t blk, int32_t (&off)[Q - 1]) {
-  const int32_t s = a.seg_base[blk] + (int32_t)ld_stream(a.seg_delta + p);
-  const int32_t first = __builtin_amdgcn_readfirstlane(s);
-  if (__ballot(s > first + 1) == 0) {
-    using CI = const __attribute__((address_space(4))) int32_t;
-    CI *r = (CI *)(a.seg_off + (int64_t)first * kSegRow);
-    const bool second = s != first;
-    // the empty asm statements hold both rows in scalar registers (else the
-    // select folds into one per-lane load from a selected address)
-#pragma unroll
-    for (int i = 0; i < Q - 1; ++i) {
-      int32_t x = r[i], y = r[kSegRow + i];
-      asm("" : "+s"(x), "+s"(y));
-      off[i] = second ? y : x;
-    }
-  } else {
-    const int4 *row = reinterpret_cast<const int4 *>(a.seg_off + (int64_t)s * kSegRow);
-    int4 rr[5];
-#pragma unroll
-    for (int k = 0; k < 5; ++k) rr[k] = row[k];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      off[4 * k] = rr[k].x;
-      off[4 * k + 1] = rr[k].y;
-      off[4 * k + 2] = rr[k].z;
-      off[4 * k + 3] = rr[k].w;
-    }
-    off[16] = rr[4].x;
-    off[17] = rr[4].y;
-  }
 }
 
 // The value iolet k applies in the update t -> t+1: a Windkessel outlet's
@@ -540,13 +529,8 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
     // offset np puts jb at or above sz np + D.
     using N = Narrow<T>;
     int32_t off[Q - 1];
-    // FP16 is bound by the vector path's address processing: there the
-    // scalar row loads took the step kernel from 0.335 to 0.330 ms on a
-    // 2e7-site tree; FP64, bound by HBM, measured 0.2% slower with them.
     if constexpr (LROWS)
       lds_offsets(lrow, off);
-    else if constexpr (sizeof(T) == 2)
-      bulk_offsets_wave(a, p, blk, off);
     else
       bulk_offsets(a, p, blk, off);
     // The empty asm statements keep pb whole (so that each jb is one

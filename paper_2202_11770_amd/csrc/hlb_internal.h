@@ -42,7 +42,7 @@ constexpr int64_t kPopTile = int64_t(1) << kPopTileShift;
 // takes 54 us with the sums spread and porous_walls() after the gathers).  The sums are folded into DevPtrs::acc[0] before that is read.
 constexpr int kFluxSlots = 4096;
 // Partial sums of the mass reduction (one per workgroup, at most).
-constexpr int64_t kMassPartials = 4096;
+constexpr int64_t kMassPartials = 4095;
 
 struct IoletDev {
   int32_t kind;     // HLB_IOLET_VELOCITY / HLB_IOLET_PRESSURE
@@ -77,8 +77,9 @@ struct Layout {
 struct DevPtrs {
   void *f[2] = {nullptr, nullptr};  // population buffers, [np/kPopTile][19][kPopTile] of the storage type
   int32_t *seg_off = nullptr;       // [nseg + 1][kSegRow] bulk+wall source offsets per segment
-                                    // (the last row is padding, read by scalar row loads)
-  int32_t *seg_base = nullptr;      // [ceil(n0 / kSegBlock)] first segment of each block
+                                    // (the last row is padding)
+  int32_t *seg_base = nullptr;      // [ceil(n0 / kSegBlock) + 1] first segment of each block; the last
+                                    // entry is the last segment
   uint8_t *seg_delta = nullptr;     // [n0] segment of each position minus its block's first
   int32_t *nbr_io = nullptr;        // iolet groups' pull table [18][nio]: source position of
                                     // population i (i = 1..18), or the link code (< 0)

@@ -37,30 +37,30 @@ using namespace dev;
 // edge blocks and the rest separately).  Every block, hence every wavefront,
 // runs one group's code path only.
 // Per storage type, measured on the 2e7-site tree: the minimum waves per
-// SIMD the step kernel is compiled for (the rare iolet blocks spill to fit,
-// the bulk path does not), and whether population addresses use 32-bit byte
+// SIMD the step kernel is compiled for, and whether population addresses use 32-bit byte
 // offsets when a buffer allows it (see at()).  FP64: the natural 4 waves and
 // 32-bit offsets; FP32: 6 waves and 64-bit addresses (32-bit offsets
 // measured 3% slower); FP16: 6 waves and 32-bit offsets.  Measured again
 // with the per-storage workgroup-to-XCD chunk on the 2e7- and 2e8-site
-// trees: FP64 4 waves (5, 6 slower by 0.5-1% on the 2e8 tree), FP16 6 (8
-// waves 0.5-1.6% slower, 5 waves 2-3%).  FP32, with the segment rows in LDS
+// trees: FP64 4 waves (5, 6 slower by 0.5-1% on the 2e8 tree).  FP16, with the
+// segment rows in LDS: 7 waves (20 bytes of scratch in the iolet path) 320.7 us
+// on the 2.0e7-site tree, 6 323.1, 8 322.2, 5 334.  FP32, with the segment rows in LDS
 // and the banded order: 6 waves against its natural 5 gave +0.2-0.3% on the
 // trees and +0.9-1.0% on the 6e8-site forest; 4 waves cost 5%.
 // SPT = 2 (two bulk+wall sites per thread, see below) needs about twice the
 // registers of the bulk path: 4 waves.
 template <typename T, int SPT = 1, bool NARROW = true>
-constexpr int kStepWaves = SPT == 2 ? 4 : (std::is_same<T, double>::value ? 4 : 6);
+constexpr int kStepWaves = SPT == 2 ? 4 : (std::is_same<T, double>::value ? 4 : sizeof(T) == 2 ? 7 : 6);
 template <typename T>
 constexpr bool kStepNarrow = !std::is_same<T, float>::value;
-// Whether the bulk path stages each block's segment rows through LDS: one
-// coalesced pass over the block's rows (typically 20-50 of them) replaces
-// every lane's five 16-byte row loads, each of which touches a cache line
-// per distinct segment of its wavefront.  FP64 and FP32: +0.4% on the 2e7-
-// and +0.5-1.3% on the 2e8-site tree.  FP16 keeps its wavefront-wide scalar
-// row loads: the staging pass and barrier cost it 3-5%.
+// The bulk path of a full step stages each block's segment rows through LDS
+// (stage_rows): FP64 and FP32 +0.4% on the 2e7- and +0.5-1.3% on the 2e8-site
+// tree against five row loads per lane, each of which touches a cache line per
+// distinct segment of its wavefront; FP16 +1.7% and +2.1% on the 7.8e6- and
+// 2.0e7-site trees with the short chain of loads (with the long one 3-5%
+// slower).
 template <typename T>
-constexpr bool kStepLdsRows = sizeof(T) != 2;
+constexpr bool kStepShortRows = sizeof(T) == 2;
 
 // SPT: bulk+wall sites per thread.  With SPT = 2 a workgroup takes two
 // consecutive 256-position blocks and each thread one position of each (both
@@ -100,24 +100,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
   } else if constexpr (SPT == 1) {
     const int64_t blk = blk0 + block_id(b - nb_io, nb_bulk, xcd_chunk);
     const int64_t p = blk * kBlock + threadIdx.x;
-    constexpr bool LROWS = kStepLdsRows<T>;
-    // rows of the block's segments: seg_base[blk] .. + seg_delta of its last
-    // position (at most kSegBlock rows)
-    __shared__ int4 lrows[LROWS ? kSegBlock * (kSegRow / 4) : 1];
-    int32_t k_row = 0;
-    if constexpr (LROWS) {
-      // p's row in the block, loaded before the pass so that the two loads'
-      // latencies overlap (no load moves across the barrier)
-      k_row = p < n0 ? (int32_t)ld_stream(a.seg_delta + p) : 0;
-      const int64_t last = blk * kBlock + kBlock - 1 < n0 ? blk * kBlock + kBlock - 1 : n0 - 1;
-      const int32_t n4 = ((int32_t)a.seg_delta[last] + 1) * (kSegRow / 4);
-      const int4 *rows = reinterpret_cast<const int4 *>(a.seg_off + (int64_t)a.seg_base[blk] * kSegRow);
-      for (int k = threadIdx.x; k < n4; k += kBlock) lrows[k] = rows[k];
-      __syncthreads();
-    }
+    __shared__ int4 lrows[kSegBlock * (kSegRow / 4)];
+    const int4 *lrow = stage_rows<kStepShortRows<T>>(a, blk, p, n0, lrows);
     if (p < n0) {
       C g[Q];
-      flux = gather<false, POROUS, SH, NARROW, LROWS>(A, p, blk, a, g, nullptr, lrows + (kSegRow / 4) * k_row);
+      flux = gather<false, POROUS, SH, NARROW, true>(A, p, blk, a, g, nullptr, lrow);
       collide<SH>(g, omega, C(a.rho0));
       if constexpr (NARROW) {
         using N = Narrow<T>;

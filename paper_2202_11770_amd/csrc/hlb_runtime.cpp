@@ -708,10 +708,9 @@ static hlb_status create_impl(int64_t n, const int32_t *coords, const uint8_t *t
     segid[p] = (int32_t)(nseg - 1);
   }
   L.nseg = nseg;
-  // one padding row after the last segment (read by a wavefront's scalar
-  // row loads, never used)
+  // one padding row after the last segment
   std::vector<int32_t> seg_off((size_t)kSegRow * (nseg + 1), 0);
-  std::vector<int32_t> seg_base(std::max<int64_t>(nb0, 1), 0);
+  std::vector<int32_t> seg_base(nb0 + 1, 0);
   std::vector<uint8_t> seg_delta((size_t)std::max<int64_t>(nb0 * kSegBlock, 1), 0);
 #pragma omp parallel for schedule(static)
   for (int64_t p = 0; p < n0; ++p) {
@@ -721,6 +720,7 @@ static hlb_status create_impl(int64_t n, const int32_t *coords, const uint8_t *t
   }
 #pragma omp parallel for schedule(static)
   for (int64_t p = 0; p < n0; ++p) seg_delta[p] = (uint8_t)(segid[p] - segid[(p / kSegBlock) * kSegBlock]);
+  seg_base[nb0] = (int32_t)std::max<int64_t>(nseg - 1, 0);
   segid.clear();
   segid.shrink_to_fit();
   c->adj_on = opt.adjoint != 0;  // the adjoint's transposed gather reads the pull tables
