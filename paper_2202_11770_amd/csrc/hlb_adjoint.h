@@ -14,8 +14,8 @@ namespace hlb {
 // (wavefront index mod kAdjJSlots), so that no single address takes one
 // atomic per wavefront of the grid.
 constexpr int64_t kAdjJSlots = 4096;
-// Length of AdjBuffers::J: [0] the objective, [1, 5) the caller's flux
-// accumulators while a sweep runs, [8, 8 + kAdjJSlots) the partial sums.
+// Length of AdjBuffers::J: [0] the objective, [8, 8 + kAdjJSlots) the partial
+// sums.
 constexpr int64_t kAdjJLen = 8 + kAdjJSlots;
 
 // Device buffers of the adjoint sweep (FP64 storage only).
@@ -24,7 +24,7 @@ struct AdjBuffers {
   // nu_{t+1} before the reverse step t and nu[1 - cur] takes nu_t
   double *nu[2] = {nullptr, nullptr};
   int cur = 0;
-  double *J = nullptr;        // [kAdjJLen] objective, saved flux accumulators, partial sums
+  double *J = nullptr;        // [kAdjJLen] objective, partial sums
   double *dA = nullptr;       // [n_iolets][n_steps]
   double *dphi = nullptr;     // [np] porosity derivative per position
   int32_t objective = HLB_OBJ_WSS;

@@ -88,15 +88,20 @@ struct DevPtrs {
   IoletDev *io = nullptr;           // [n_iolets]
   double *tables = nullptr;         // concatenated per-step iolet tables
   double *phi = nullptr;            // [np] porosity, or null
-  double *acc = nullptr;            // [4] FP64 accumulators: boundary flux since t0 up to the last fold, ...
+  double *acc = nullptr;            // [4]: boundary flux since t0 up to the last fold; ...; [3] the
+                                    // step kernel's count of finished iolet blocks (zero between launches)
   double *flux = nullptr;           // [kFluxSlots] boundary flux since the last fold (see kFluxSlots);
                                     // the tail of the allocation of `partial`
   double *partial = nullptr;        // [partial_len] reduction scratch
   int64_t partial_len = 0;
   double *io_scratch = nullptr;     // [np*19] host-exchange staging (allocated lazily)
-  double *wk_rho = nullptr;         // [n_iolets][2] Windkessel densities by time parity
+  // Windkessel outlets: an update reads the models' state in wk (densities by
+  // time parity, [n_iolets][2], in wk_rho) and writes it to wk_next, which is
+  // the same arrays but at the ends of an adjoint's checkpoint
+  WkParams *wk = nullptr, *wk_next = nullptr;      // [n_iolets]
+  double *wk_rho = nullptr, *wk_rho_next = nullptr;
   double *io_flux = nullptr;        // [n_iolets] outflow of the current update (Windkessel outlets)
-  WkParams *wk = nullptr;           // [n_iolets]
+  int wk_n = 0;                     // n_iolets while a Windkessel outlet is on, else 0
   // Set only in the copies a replayed graph is captured with: the kernels
   // then take the time as *t_base + t (t = the step's index in the graph),
   // so that one graph serves every starting time.
@@ -119,7 +124,9 @@ struct LaunchCfg {
 int default_sites_per_thread(int storage);
 
 // ---- launchers (hlb_kernels.hip); all asynchronous on `s` ----
-// One update t -> t+1: reads buffer `src`, writes buffer 1-src.
+// One update t -> t+1: reads buffer `src`, writes buffer 1-src.  Windkessel
+// outlets (d.wk_n > 0) then take their outflow, advance their state and set
+// the density of the update t+1 -> t+2.
 // ev_begin / ev_end (may be null) are recorded around the step kernel.
 hipError_t launch_step(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, int src, int64_t t,
                        hipStream_t s, hipEvent_t e0, hipEvent_t e1, int part = 0);
@@ -146,10 +153,6 @@ hipError_t launch_set_state(const LaunchCfg &cfg, const Layout &L, const DevPtrs
 hipError_t launch_fold_flux(double *acc, double *flux, hipStream_t s);
 // p[0..n) := 0 (a kernel, so that no memset node lands in a captured graph).
 hipError_t launch_zero(double *p, int64_t n, hipStream_t s);
-// After the update t -> t+1: Windkessel outlets take their outflow, advance
-// their state and set the density of the update t+1 -> t+2; the outflow
-// accumulators are cleared (no memset: the launch may be graph-captured).
-hipError_t launch_windkessel(const DevPtrs &d, int n_io, int64_t t, hipStream_t s);
 // *p = v, and *p += k (one thread each; a kernel, not a memset, so that the
 // second can sit in a captured graph).
 hipError_t launch_set_time(int64_t *p, int64_t v, hipStream_t s);

@@ -70,7 +70,8 @@ constexpr bool kStepShortRows = sizeof(T) == 2;
 template <typename T, bool POROUS, bool NARROW, int SPT = 1>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T, SPT, NARROW>, 8))) void k_step(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
-    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots) {
+    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots,
+    uint32_t *done) {
   using C = typename Acc<T>::type;
   constexpr bool SH = kShifted<T>;
   const int64_t b = blockIdx.x;
@@ -96,7 +97,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
       flux = 0;
     }
     add_flux(flux_slots, double(flux));
-    if (a.io_flux) wave_add_grouped(a.io_flux, wkf);
+    if (a.wk_n > 0) {
+      wave_add_grouped(a.io_flux, wkf);
+      finish_outlets(a, nb_io, done);
+    }
   } else if constexpr (SPT == 1) {
     const int64_t blk = blk0 + block_id(b - nb_io, nb_bulk, xcd_chunk);
     const int64_t p = blk * kBlock + threadIdx.x;
@@ -148,7 +152,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
 template <typename T, bool POROUS, bool NARROW>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T>, 8))) void k_step_push(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
-    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots) {
+    int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots,
+    uint32_t *done) {
   using C = typename Acc<T>::type;
   constexpr bool SH = kShifted<T>;
   const int64_t b = blockIdx.x;
@@ -166,7 +171,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
       flux = scatter<true, POROUS, SH, NARROW>(B, p, 0, a, f, jx / rho, jy / rho, jz / rho, rho, &wkf);
     }
     add_flux(flux_slots, double(flux));
-    if (a.io_flux) wave_add_grouped(a.io_flux, wkf);
+    if (a.wk_n > 0) {
+      wave_add_grouped(a.io_flux, wkf);
+      finish_outlets(a, nb_io, done);
+    }
   } else {
     const int64_t blk = blk0 + block_id(b - nb_io, nb_bulk, xcd_chunk);
     const int64_t p = blk * kBlock + threadIdx.x;
@@ -360,22 +368,10 @@ __global__ __launch_bounds__(kBlock) void k_mass_final(double *partial, int64_t 
   }
 }
 
-// One thread per iolet (see launch_windkessel).  t_base: as in GatherArgs.
-__global__ void k_windkessel(const IoletDev *io, WkParams *wk, double *wk_rho, double *io_flux, int n_io,
-                             int64_t t, const int64_t *t_base) {
+// The Windkessel outlets of a step without iolet blocks (one thread each).
+__global__ void k_windkessel(GatherArgs a) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= n_io || !io[k].wk) return;
-  if (t_base) t += *t_base;
-  const double Q = io_flux[k];
-  io_flux[k] = 0.0;
-  WkParams P = wk[k];
-  if (P.C > 0.0)
-    P.X += (Q - (P.R2 > 0.0 ? P.X / P.R2 : 0.0)) / P.C;
-  else
-    P.X = P.R2 * Q;
-  P.Q = Q;
-  wk[k] = P;
-  wk_rho[2 * k + ((t + 1) & 1)] = P.rho_ref + P.R1 * Q + P.X;
+  if (k < a.wk_n) windkessel(a, k, step_time(a), a.io_flux[k]);
 }
 
 __global__ void k_set_time(int64_t *p, int64_t v) { *p = v; }
@@ -420,6 +416,7 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
   if (e0 && (er = hipEventRecord(e0, s)) != hipSuccess) return er;
   // byte offsets fit in 32 bits when a whole population buffer does, with
   // the bias of the bulk path's addressing (Narrow)
+  uint32_t *done = reinterpret_cast<uint32_t *>(d.acc + 3);
   const bool narrow = kStepNarrow<T> && (uint64_t)Q * (uint64_t)L.np * sizeof(T) + Narrow<T>::BIAS <=
                                             (uint64_t(1) << 32);
   if (grid > 0) {
@@ -427,13 +424,13 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
   do {                                                                                                  \
     if (cfg.scheme == HLB_SCHEME_PUSH)                                                                  \
       k_step_push<T, P, N><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk,          \
-                                                   cfg.xcd_chunk, omega, d.flux);                        \
+                                                   cfg.xcd_chunk, omega, d.flux, done);                        \
     else if (pair)                                                                                      \
       k_step<T, P, N, 2><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, 0, nb_launch,             \
-                                                 cfg.xcd_chunk, omega, d.flux);                          \
+                                                 cfg.xcd_chunk, omega, d.flux, done);                          \
     else                                                                                                \
       k_step<T, P, N><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk, cfg.xcd_chunk, \
-                                              omega, d.flux);                                            \
+                                              omega, d.flux, done);                                            \
   } while (0)
     if (cfg.porous) {
       if (narrow) HLB_STEP(true, kStepNarrow<T>);
@@ -444,6 +441,8 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
     }
 #undef HLB_STEP
   }
+  if ((er = hipGetLastError()) != hipSuccess) return er;
+  if (a.wk_n > 0 && part == 0 && nb_io == 0) k_windkessel<<<(a.wk_n + 63) / 64, 64, 0, s>>>(a);
   if ((er = hipGetLastError()) != hipSuccess) return er;
   if (e1 && (er = hipEventRecord(e1, s)) != hipSuccess) return er;
   return hipSuccess;
@@ -560,12 +559,6 @@ hipError_t launch_macros(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d
 hipError_t launch_set_state(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, int pre,
                             const double *staging, hipStream_t s) {
   HLB_DISPATCH(cfg.storage, set_state_impl<T>(cfg, L, d, pre, staging, s));
-}
-
-hipError_t launch_windkessel(const DevPtrs &d, int n_io, int64_t t, hipStream_t s) {
-  if (n_io <= 0 || !d.wk) return hipSuccess;
-  k_windkessel<<<(n_io + 63) / 64, 64, 0, s>>>(d.io, d.wk, d.wk_rho, d.io_flux, n_io, t, d.t_base);
-  return hipGetLastError();
 }
 
 hipError_t launch_set_time(int64_t *p, int64_t v, hipStream_t s) {

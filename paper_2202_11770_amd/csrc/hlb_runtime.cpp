@@ -154,7 +154,7 @@ bool same_launch(const DevPtrs &a, const DevPtrs &b) {
   return a.f[0] == b.f[0] && a.f[1] == b.f[1] && a.seg_off == b.seg_off && a.seg_base == b.seg_base &&
          a.seg_delta == b.seg_delta && a.nbr_io == b.nbr_io && a.order == b.order && a.corr == b.corr &&
          a.io == b.io && a.tables == b.tables && a.phi == b.phi && a.acc == b.acc && a.flux == b.flux && a.wk_rho == b.wk_rho &&
-         a.io_flux == b.io_flux && a.wk == b.wk;
+         a.io_flux == b.io_flux && a.wk == b.wk && a.wk_n == b.wk_n;
 }
 bool same_launch(const LaunchCfg &a, const LaunchCfg &b) {
   return a.storage == b.storage && a.tau == b.tau && a.rho0 == b.rho0 && a.xcd_chunk == b.xcd_chunk &&
@@ -328,6 +328,7 @@ void free_all(hlb_ctx *c) {
 hlb_status upload_tables(hlb_ctx *c) {
   const int K = (int)c->iolets.size();
   if (K == 0) return HLB_OK;
+  c->d.wk_n = c->n_wk > 0 ? K : 0;
   HIP_TRY(hipStreamSynchronize(c->stream));
   // tables last set from device memory live only in d.tables: fetch them
   // before the concatenation is rebuilt
@@ -895,9 +896,9 @@ hlb_status hlb_set_windkessel(hlb_ctx *c, int32_t k, const hlb_windkessel *w) {
   if (!c->d.wk) {
     void *p = nullptr;
     if (hlb_status st = dev_alloc(c, &p, (size_t)K * sizeof(WkParams))) return st;
-    c->d.wk = static_cast<WkParams *>(p);
+    c->d.wk = c->d.wk_next = static_cast<WkParams *>(p);
     if (hlb_status st = dev_alloc(c, &p, (size_t)2 * K * sizeof(double))) return st;
-    c->d.wk_rho = static_cast<double *>(p);
+    c->d.wk_rho = c->d.wk_rho_next = static_cast<double *>(p);
     if (hlb_status st = dev_alloc(c, &p, (size_t)K * sizeof(double))) return st;
     c->d.io_flux = static_cast<double *>(p);
     std::vector<double> z((size_t)2 * K, 0.0);
@@ -1305,7 +1306,6 @@ hlb_status capture_steps(hlb_ctx *c, int cur) {
   hipError_t e = hipSuccess;
   for (int k = 0; k < c->graph_steps && e == hipSuccess; ++k) {
     e = launch_step(c->cfg, c->L, d, (cur + k) & 1, k, c->cap_stream, nullptr, nullptr);
-    if (e == hipSuccess && c->n_wk > 0) e = launch_windkessel(d, (int)c->iolets.size(), k, c->cap_stream);
   }
   if (e == hipSuccess) e = launch_add_time(c->t_dev, c->graph_steps, c->cap_stream);
   hipGraph_t g = nullptr;
@@ -1368,7 +1368,6 @@ hlb_status hlb_step(hlb_ctx *c, int64_t n) {
       e1 = ts.e[1];
     }
     HIP_TRY(launch_step(c->cfg, c->L, c->d, c->cur, c->t, c->stream, e0, e1));
-    if (c->n_wk > 0) HIP_TRY(launch_windkessel(c->d, (int)c->iolets.size(), c->t, c->stream));
     c->cur = 1 - c->cur;
     c->direct = false;
     c->t += 1;
@@ -1737,27 +1736,42 @@ struct Revolve {
   int64_t t0, n, w0, w1, n_snap;
   std::vector<int64_t> slot_t;
   int64_t fwd = 0;
-  // The current state may live in a checkpoint slot instead of the
-  // context's own buffer: a restore only points at the slot, the next forward
-  // step pulls from it into a context buffer (or the adjoint step reads it
-  // there), and a checkpoint's forward run writes its last step straight into
-  // the slot.  No slot is written while it is read, so restores and
-  // checkpoints cost no copy.
-  const void *in_slot = nullptr;
+  // A checkpoint slot: the post-collision state and the Windkessel outlets'
+  // state.  Slot 0 is the caller's own state, which the sweep only reads.
+  struct Slot {
+    void *f;
+    WkParams *wk;
+    double *wk_rho;
+  };
+  std::vector<Slot> slots;
+  // The current state may live in a checkpoint slot instead of the sweep's
+  // work buffers (the context's d while the sweep runs): a restore only points
+  // at the slot, the next forward step pulls from it into a work buffer (or the
+  // adjoint step reads it there), and a checkpoint's forward run writes its last
+  // step straight into the slot.  No slot is written while it is read, so
+  // restores and checkpoints cost no copy.
+  const Slot *in_slot = nullptr;
 
   DevPtrs reading_slot() const {
     DevPtrs d = c->d;
-    if (in_slot) d.f[c->cur] = const_cast<void *>(in_slot);
+    if (in_slot) {
+      d.f[c->cur] = in_slot->f;
+      d.wk = in_slot->wk;
+      d.wk_rho = in_slot->wk_rho;
+    }
     return d;
   }
   // k forward steps; with `last_dst`, the last one writes into that slot.
-  hlb_status advance(int64_t k, void *last_dst = nullptr) {
+  hlb_status advance(int64_t k, const Slot *last_dst = nullptr) {
     for (int64_t s = 0; s < k; ++s) {
       DevPtrs d = reading_slot();
-      void *dst = (last_dst && s == k - 1) ? last_dst : nullptr;
-      if (dst) d.f[1 - c->cur] = dst;
+      const Slot *dst = (last_dst && s == k - 1) ? last_dst : nullptr;
+      if (dst) {
+        d.f[1 - c->cur] = dst->f;
+        d.wk_next = dst->wk;
+        d.wk_rho_next = dst->wk_rho;
+      }
       HIP_TRY(launch_step(c->cfg, c->L, d, c->cur, c->t, c->stream, nullptr, nullptr));
-      if (c->n_wk > 0) HIP_TRY(launch_windkessel(c->d, (int)c->iolets.size(), c->t, c->stream));
       in_slot = dst;
       c->cur = 1 - c->cur;
       c->t += 1;
@@ -1765,33 +1779,11 @@ struct Revolve {
     fwd += k;
     return HLB_OK;
   }
-  // the Windkessel outlets' state to (or from) checkpoint slot `slot`
-  hlb_status wk_state(int64_t slot, bool to_slot) {
-    if (c->n_wk <= 0) return HLB_OK;
-    const size_t nio = c->iolets.size(), pb = nio * sizeof(WkParams), rb = 2 * nio * sizeof(double);
-    char *base = static_cast<char *>(c->adj_wk_slots) + (size_t)slot * (pb + rb);
-    if (to_slot) {
-      HIP_TRY(hipMemcpyAsync(base, c->d.wk, pb, hipMemcpyDeviceToDevice, c->stream));
-      HIP_TRY(hipMemcpyAsync(base + pb, c->d.wk_rho, rb, hipMemcpyDeviceToDevice, c->stream));
-    } else {
-      HIP_TRY(hipMemcpyAsync(c->d.wk, base, pb, hipMemcpyDeviceToDevice, c->stream));
-      HIP_TRY(hipMemcpyAsync(c->d.wk_rho, base + pb, rb, hipMemcpyDeviceToDevice, c->stream));
-    }
-    return HLB_OK;
-  }
-  hlb_status save(int64_t slot) {
-    const void *src = in_slot ? in_slot : c->d.f[c->cur];
-    if (src != c->adj_slots[slot])
-      HIP_TRY(hipMemcpyAsync(c->adj_slots[slot], src, buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
-    slot_t[slot] = c->t;
-    return wk_state(slot, true);
-  }
-  hlb_status restore(int64_t slot) {
-    in_slot = c->adj_slots[slot];
+  void restore(int64_t slot) {
+    in_slot = &slots[slot];
     c->cur = 0;
     c->t = slot_t[slot];
     c->direct = false;
-    return wk_state(slot, false);
   }
   hlb_status adjoint_step(int64_t t) {  // needs the state of time t-1
     const int in_window = (t > w0 && t <= w1) ? 1 : 0;
@@ -1817,15 +1809,14 @@ struct Revolve {
     while (b - a > 1 && cfree > 0) {
       const int64_t m = a + revolve_split(b - a, cfree + 1);
       const int64_t slot_m = n_snap - cfree;
-      if (hlb_status st = restore(slot_a)) return st;
-      if (hlb_status st = advance(m - a, c->adj_slots[slot_m])) return st;  // m - a >= 1
+      restore(slot_a);
+      if (hlb_status st = advance(m - a, &slots[slot_m])) return st;  // m - a >= 1
       slot_t[slot_m] = c->t;
-      if (hlb_status st = wk_state(slot_m, true)) return st;
       if (hlb_status st = reverse(m, b, slot_m, cfree - 1)) return st;
       b = m;
     }
     for (int64_t t = b; t > a; --t) {  // no free slot left (or one step): recompute from a
-      if (hlb_status st = restore(slot_a)) return st;
+      restore(slot_a);
       if (hlb_status st = advance(t - 1 - a)) return st;
       if (hlb_status st = adjoint_step(t)) return st;
     }
@@ -1862,7 +1853,6 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
     c->adj.nu[1] = static_cast<double *>(p);
     if (hlb_status st = dev_alloc(c, &p, (size_t)np * sizeof(double))) return st;
     c->adj.dphi = static_cast<double *>(p);
-    // [0] the objective; [1, 5) the caller's flux accumulators while the sweep runs
     if (hlb_status st = dev_alloc(c, &p, kAdjJLen * sizeof(double))) return st;
     c->adj.J = static_cast<double *>(p);
     if (hlb_status st = dev_alloc(c, &p, (size_t)std::max<int64_t>(1, nio) * sizeof(double))) return st;
@@ -1895,29 +1885,57 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
     c->adj.dA = static_cast<double *>(p);
     c->adj_dA_len = std::max<int64_t>(1, nio * n);
   }
-  // checkpoint slots, plus one for the caller's other population buffer
+  // the checkpoint slots but the first, and two work buffers
   while ((int64_t)c->adj_slots.size() < (int64_t)n_snap + 1) {
     if (hlb_status st = dev_alloc(c, &p, buf_bytes(c))) return st;
     c->adj_slots.push_back(p);
   }
-  // keep the caller's state: both buffers, time, flags, flux accumulator
+  // The caller's state stays where it is: the sweep reads its buffer as
+  // checkpoint slot 0 and steps in buffers, model state and flux sums of its own,
+  // which stand in for the context's while it runs.
+  const DevPtrs d0 = c->d;
   const int cur0 = c->cur;
   const bool direct0 = c->direct;
   const int64_t t_start = c->t;
-  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->adj.J + 1, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->adj_slots[n_snap], c->d.f[1 - cur0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
+  Revolve R;
+  R.slots.resize(n_snap);
+  for (int64_t k = 0; k < n_snap; ++k) {
+    const int64_t region = k + 1;  // region 0: the work state
+    char *w = static_cast<char *>(c->adj_wk_slots);
+    const size_t pb = (size_t)nio * sizeof(WkParams), rb = 2 * (size_t)nio * sizeof(double);
+    R.slots[k].f = c->adj_slots[k];  // slot 0's buffer is a work buffer
+    R.slots[k].wk = c->n_wk > 0 ? reinterpret_cast<WkParams *>(w + region * (pb + rb)) : nullptr;
+    R.slots[k].wk_rho = c->n_wk > 0 ? reinterpret_cast<double *>(w + region * (pb + rb) + pb) : nullptr;
+  }
+  R.slots[0] = {d0.f[cur0], d0.wk, d0.wk_rho};
+  c->d.f[0] = c->adj_slots[0];
+  c->d.f[1] = c->adj_slots[n_snap];
+  if (c->n_wk > 0) {
+    c->d.wk = c->d.wk_next = static_cast<WkParams *>(c->adj_wk_slots);
+    c->d.wk_rho = c->d.wk_rho_next =
+        reinterpret_cast<double *>(static_cast<char *>(c->adj_wk_slots) + (size_t)nio * sizeof(WkParams));
+  }
+  static_assert(kFluxSlots <= 1 + kMassPartials, "the reduction scratch takes the sweep's flux sums");
+  c->d.flux = c->d.partial;  // discarded
+  auto restore = [&]() {
+    c->d = d0;
+    c->cur = cur0;
+    c->direct = direct0;
+    c->t = t_start;
+  };
   // nu past the last step, and mu there in the iolet groups' slots of the
   // other buffer (whole tiles from the one where the groups begin)
   const int64_t io_tile = c->L.io_begin / kPopTile * kPopTile;
   c->adj.cur = 0;
-  HIP_TRY(launch_zero(c->adj.nu[0], (int64_t)Q * np, c->stream));
-  HIP_TRY(launch_zero(c->adj.nu[1] + Q * io_tile, Q * (np - io_tile), c->stream));
-  HIP_TRY(launch_zero(c->adj.dphi, np, c->stream));
-  HIP_TRY(launch_zero(c->adj.J + 8, kAdjJSlots, c->stream));
-  HIP_TRY(launch_zero(c->adj.dA, std::max<int64_t>(1, nio * n), c->stream));
-  HIP_TRY(launch_zero(c->adj.lamX, std::max<int64_t>(1, nio), c->stream));
-  Revolve R;
+  auto clear = [&]() -> hlb_status {
+    HIP_TRY(launch_zero(c->adj.nu[0], (int64_t)Q * np, c->stream));
+    HIP_TRY(launch_zero(c->adj.nu[1] + Q * io_tile, Q * (np - io_tile), c->stream));
+    HIP_TRY(launch_zero(c->adj.dphi, np, c->stream));
+    HIP_TRY(launch_zero(c->adj.J + 8, kAdjJSlots, c->stream));
+    HIP_TRY(launch_zero(c->adj.dA, std::max<int64_t>(1, nio * n), c->stream));
+    HIP_TRY(launch_zero(c->adj.lamX, std::max<int64_t>(1, nio), c->stream));
+    return HLB_OK;
+  };
   R.c = c;
   R.t0 = t_start;
   R.n = n;
@@ -1925,26 +1943,14 @@ hlb_status adjoint_sweep(hlb_ctx *c, int64_t n, int64_t obj_t0, int64_t obj_t1, 
   R.w1 = obj_t1;
   R.n_snap = n_snap;
   R.slot_t.assign(n_snap, 0);
-  hlb_status st = R.save(0);
+  R.slot_t[0] = t_start;
+  hlb_status st = clear();
   if (!st) st = R.reverse(t_start, t_start + n, 0, n_snap - 1);
   if (!st) {
     hipError_t e = launch_adjoint_objective(c->adj.J, c->stream);
     if (e != hipSuccess) st = fail(HLB_EDEVICE, "objective sum: %s", hipGetErrorString(e));
   }
-  // put the caller's state back
-  if (!st) {
-    hipError_t e = hipMemcpyAsync(c->d.f[cur0], c->adj_slots[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(c->d.f[1 - cur0], c->adj_slots[n_snap], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(c->d.acc, c->adj.J + 1, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
-    if (e == hipSuccess) e = launch_zero(c->d.flux, kFluxSlots, c->stream);
-    if (e != hipSuccess) st = fail(HLB_EDEVICE, "restoring the state: %s", hipGetErrorString(e));
-    if (!st) st = R.wk_state(0, false);
-  }
-  c->cur = cur0;
-  c->direct = direct0;
-  c->t = t_start;
+  restore();
   if (!st && forward_steps) *forward_steps = R.fwd;
   return st;
 }
