@@ -244,87 +244,108 @@ __global__ __launch_bounds__(kBlock) void k_set_state(T *__restrict__ Pre, T *__
 
 // --------------------------------------------------------------- macros ----
 
-// Density, velocity, wall shear stress (or the populations) of the
-// pre-collision state at time t, in FP64, written per caller id.
-template <typename T, bool POROUS>
-__global__ __launch_bounds__(kBlock) void k_macros(const T *__restrict__ A, GatherArgs a,
-                                                   const int32_t *__restrict__ order, int direct,
-                                                   double tau, double *rho_o, double *u_o,
-                                                   double *wss_o, double *f_o) {
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (p >= a.np) return;
+// Density, velocity, wall shear stress (STATE: the populations) of the
+// pre-collision state at time t, in FP64, written per caller id.  Bound by HBM:
+// the gather of a step, 40 bytes written per site and its caller id.  Blocks
+// and addresses are the step kernel's (iolet groups first, XCD chunks,
+// segment rows in LDS, 32-bit offsets where a buffer allows), and the stress
+// is formed from six moments, only where a wavefront has wall sites, so that
+// the kernel runs at 4 waves per SIMD instead of 2: 862 -> 824 us on the 2.0e7-site
+// tree in FP64, 722 -> 556 in FP32, 282 -> 199 on the 7.8e6-site tree in FP16, 8.4 ->
+// 6.7 on the 13,312-site pipe (5 waves spill: 917 us).
+template <typename T, bool POROUS, bool NARROW, bool STATE>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_macros(
+    const T *__restrict__ A, GatherArgs a, const int32_t *__restrict__ order, int64_t n0, int64_t nb_io, int64_t nb_bulk,
+    int xcd_chunk, int direct, double tau, double *__restrict__ rho_o, double *__restrict__ u_o,
+    double *__restrict__ wss_o, double *__restrict__ f_o) {
+  const int64_t b = blockIdx.x;
+  const bool bulk = b >= nb_io;
+  const int64_t blk = bulk ? block_id(b - nb_io, nb_bulk, xcd_chunk) : a.io_begin / kBlock + b;
+  const int64_t p = blk * kBlock + threadIdx.x;
+  __shared__ int4 lrows[kSegBlock * (kSegRow / 4)];
+  const int4 *lrow = bulk ? stage_rows<kStepShortRows<T>>(a, blk, p, n0, lrows) : nullptr;
+  if (bulk && p >= n0) return;
   const int32_t id = order[p];
-  if (id < 0) return;
+  const int32_t p32 = (int32_t)p;
   constexpr bool SH = kShifted<T>;
   double g[Q];
   if (direct) {
 #pragma unroll
-    for (int i = 0; i < Q; ++i) g[i] = ld(A + pidx((int32_t)p, i));
-  } else if (p < a.io_begin) {
-    gather<false, POROUS, SH>(A, p, p / kBlock, a, g);
+    for (int i = 0; i < Q; ++i) g[i] = ld(at<NARROW>(A, p32, i));
+  } else if (bulk) {
+    gather<false, POROUS, SH, NARROW, true>(A, p, blk, a, g, nullptr, lrow);
   } else {
-    gather<true, POROUS, SH>(A, p, 0, a, g);
+    gather_iolet<POROUS, SH, NARROW>(A, p, a, g, nullptr);
   }
-  if (f_o) {
+  if (id < 0) return;
+  if constexpr (STATE) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) f_o[(int64_t)id * Q + i] = g[i] + shift<SH>(i, a.rho0);
     return;
   }
-  double dr, rho, jx, jy, jz;
-  moments<SH>(g, a.rho0, dr, rho, jx, jy, jz);
-  const double ux = jx / rho, uy = jy / rho, uz = jz / rho;
+  double dr, rho, ux, uy, uz;
+  moments<SH>(g, a.rho0, dr, rho, ux, uy, uz);
+  ux = ux / rho;
+  uy = uy / rho;
+  uz = uz / rho;
   if (rho_o) rho_o[id] = rho;
   if (u_o) {
-    u_o[3 * (int64_t)id] = ux;
-    u_o[3 * (int64_t)id + 1] = uy;
-    u_o[3 * (int64_t)id + 2] = uz;
+    // 24 bytes at 8-byte alignment in two stores
+    typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+    double *o = u_o + 3 * (int64_t)id;
+    *reinterpret_cast<d2 *>(o) = d2{ux, uy};
+    o[2] = uz;
   }
   if (!wss_o) return;
-  // wall normal: normalised sum of the directions whose links hit a wall;
-  // pull entry i describes the link leaving along opp(i) = -c_i (a wall
-  // link is coded -1 in the iolet groups, outside [0, np) in the bulk group)
-  double nx = 0, ny = 0, nz = 0;
-  bool any = false;
-  const bool bulk = p < a.io_begin;
-  int32_t off[Q - 1];
-  if (bulk) bulk_offsets(a, p, p / kBlock, off);
+  // wall links (bit i: the pull entry of direction i, which describes the
+  // link leaving along opp(i) = -c_i)
+  uint32_t walls = 0;
+  if (bulk) {
+    int32_t off[Q - 1];
+    lds_offsets(lrow, off);
 #pragma unroll
-  for (int i = 1; i < Q; ++i) {
-    const bool wall = bulk ? (uint64_t)(p + (int64_t)off[i - 1]) >= (uint64_t)a.np
-                           : a.nbr_io[(int64_t)(i - 1) * a.nio + (p - a.io_begin)] == HLB_LINK_WALL;
-    if (wall) {
-      any = true;
-      nx -= cx(i);
-      ny -= cy(i);
-      nz -= cz(i);
-    }
+    for (int i = 1; i < Q; ++i) walls |= (uint32_t)((uint32_t)(p32 + off[i - 1]) >= (uint32_t)a.np) << i;
+  } else {
+    int32_t code[Q];
+    load_codes(a, (uint32_t)(p - a.io_begin), code);
+#pragma unroll
+    for (int i = 1; i < Q; ++i) walls |= (uint32_t)(code[i] == HLB_LINK_WALL) << i;
   }
   double w = 0.0;
-  const double nn = sqrt(nx * nx + ny * ny + nz * nz);
-  if (any && nn > 0.0) {
-    nx /= nn;
-    ny /= nn;
-    nz /= nn;
-    const double usq = 1.5 * (ux * ux + uy * uy + uz * uz);
-    double pxx = 0, pyy = 0, pzz = 0, pxy = 0, pxz = 0, pyz = 0;
+  if (walls) {
+    // wall normal: normalised sum of the directions whose links hit a wall
+    int sx = 0, sy = 0, sz = 0;
 #pragma unroll
-    for (int i = 0; i < Q; ++i) {
-      // non-equilibrium part f - f_eq (the same in either representation)
-      const double d = g[i] - s_eq<SH>(i, dr, rho, ux, uy, uz, usq);
-      pxx += d * cx(i) * cx(i);
-      pyy += d * cy(i) * cy(i);
-      pzz += d * cz(i) * cz(i);
-      pxy += d * cx(i) * cy(i);
-      pxz += d * cx(i) * cz(i);
-      pyz += d * cy(i) * cz(i);
+    for (int i = 1; i < Q; ++i) {
+      const int on = (int)((walls >> i) & 1u);
+      sx -= on * cx(i);
+      sy -= on * cy(i);
+      sz -= on * cz(i);
     }
-    const double fac = -(1.0 - 1.0 / (2.0 * tau));
-    const double tx = fac * (pxx * nx + pxy * ny + pxz * nz);
-    const double ty = fac * (pxy * nx + pyy * ny + pyz * nz);
-    const double tz = fac * (pxz * nx + pyz * ny + pzz * nz);
-    const double tn = tx * nx + ty * ny + tz * nz;
-    const double sx = tx - tn * nx, sy = ty - tn * ny, sz = tz - tn * nz;
-    w = sqrt(sx * sx + sy * sy + sz * sz);
+    const double nn = sqrt((double)(sx * sx + sy * sy + sz * sz));
+    if (nn > 0.0) {
+      const double nx = sx / nn, ny = sy / nn, nz = sz / nn;
+      // non-equilibrium second moment sum (f - f_eq) c c = sum (f - w rho) c c - rho u u
+      double pxx = -rho * ux * ux, pyy = -rho * uy * uy, pzz = -rho * uz * uz;
+      double pxy = -rho * ux * uy, pxz = -rho * ux * uz, pyz = -rho * uy * uz;
+#pragma unroll
+      for (int i = 1; i < Q; ++i) {
+        const double d = g[i] - wgt<double>(i) * dr;  // dr = rho - rho0 (rho unshifted), g alike
+        if (cx(i)) pxx += d;
+        if (cy(i)) pyy += d;
+        if (cz(i)) pzz += d;
+        if (cx(i) && cy(i)) pxy += cx(i) * cy(i) > 0 ? d : -d;
+        if (cx(i) && cz(i)) pxz += cx(i) * cz(i) > 0 ? d : -d;
+        if (cy(i) && cz(i)) pyz += cy(i) * cz(i) > 0 ? d : -d;
+      }
+      const double fac = -(1.0 - 1.0 / (2.0 * tau));
+      const double tx = fac * (pxx * nx + pxy * ny + pxz * nz);
+      const double ty = fac * (pxy * nx + pyy * ny + pyz * nz);
+      const double tz = fac * (pxz * nx + pyz * ny + pzz * nz);
+      const double tn = tx * nx + ty * ny + tz * nz;
+      const double vx = tx - tn * nx, vy = ty - tn * ny, vz = tz - tn * nz;
+      w = sqrt(vx * vx + vy * vy + vz * vz);
+    }
   }
   wss_o[id] = w;
 }
@@ -392,6 +413,13 @@ __global__ void k_zero(double *p, int64_t n) {
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
+// Byte offsets fit in 32 bits when a whole population buffer does, with the
+// bias of the bulk path's addressing (Narrow).
+template <typename T>
+bool use_narrow(const Layout &L) {
+  return kStepNarrow<T> && (uint64_t)Q * (uint64_t)L.np * sizeof(T) + Narrow<T>::BIAS <= (uint64_t(1) << 32);
+}
+
 template <typename T>
 hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, int src, int64_t t,
                      hipStream_t s, hipEvent_t e0, hipEvent_t e1, int part) {
@@ -414,11 +442,8 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
   const unsigned grid = (unsigned)(nb_io + nb_launch);
   hipError_t er;
   if (e0 && (er = hipEventRecord(e0, s)) != hipSuccess) return er;
-  // byte offsets fit in 32 bits when a whole population buffer does, with
-  // the bias of the bulk path's addressing (Narrow)
+  const bool narrow = use_narrow<T>(L);
   uint32_t *done = reinterpret_cast<uint32_t *>(d.acc + 3);
-  const bool narrow = kStepNarrow<T> && (uint64_t)Q * (uint64_t)L.np * sizeof(T) + Narrow<T>::BIAS <=
-                                            (uint64_t(1) << 32);
   if (grid > 0) {
 #define HLB_STEP(P, N)                                                                                    \
   do {                                                                                                  \
@@ -486,12 +511,27 @@ hipError_t macros_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, 
   const T *A = static_cast<const T *>(d.f[src]);
   GatherArgs a = make_args(cfg, L, d, t_prev < 0 ? 0 : t_prev);
   a.io_flux = nullptr;  // the re-gather does not count towards the outflow
-  if (cfg.porous)
-    k_macros<T, true><<<blocks_for(L.np), kBlock, 0, s>>>(A, a, d.order, direct ? 1 : 0, cfg.tau, rho, u,
-                                                          wss, f_out);
-  else
-    k_macros<T, false><<<blocks_for(L.np), kBlock, 0, s>>>(A, a, d.order, direct ? 1 : 0, cfg.tau, rho, u,
-                                                           wss, f_out);
+  const int64_t n0 = L.gcnt[0], nb_bulk = (n0 + kBlock - 1) / kBlock;
+  const int64_t nb_io = (L.gbeg[kGroups] - L.io_begin) / kBlock;
+  const unsigned grid = (unsigned)(nb_io + nb_bulk);
+  const bool narrow = use_narrow<T>(L);
+#define HLB_MACROS(P, N)                                                                                             \
+  do {                                                                                                               \
+    if (f_out)                                                                                                       \
+      k_macros<T, P, N, true><<<grid, kBlock, 0, s>>>(A, a, d.order, n0, nb_io, nb_bulk, cfg.xcd_chunk,              \
+                                                      direct ? 1 : 0, cfg.tau, rho, u, wss, f_out);                  \
+    else                                                                                                             \
+      k_macros<T, P, N, false><<<grid, kBlock, 0, s>>>(A, a, d.order, n0, nb_io, nb_bulk, cfg.xcd_chunk,             \
+                                                       direct ? 1 : 0, cfg.tau, rho, u, wss, f_out);                 \
+  } while (0)
+  if (cfg.porous) {
+    if (narrow) HLB_MACROS(true, kStepNarrow<T>);
+    else HLB_MACROS(true, false);
+  } else {
+    if (narrow) HLB_MACROS(false, kStepNarrow<T>);
+    else HLB_MACROS(false, false);
+  }
+#undef HLB_MACROS
   return hipGetLastError();
 }
 
