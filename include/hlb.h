@@ -125,10 +125,11 @@ typedef struct {
                           each of the 8 XCDs gets K consecutive 256-position
                           blocks of every window of 8K blocks; 0: plain block
                           order; -1 (default): chosen by the library from the
-                          storage and the buffer size (FP16 0; FP64 64, or 256
-                          when a population buffer exceeds 4 GiB; FP32 8, or
-                          128); hlb_info reports the value in use.  Results do
-                          not depend on it. */
+                          storage and the buffer size (32 while both buffers
+                          take 208 MB at most; beyond that FP16 0; FP64 64, or
+                          256 when a population buffer exceeds 4 GiB; FP32 8,
+                          or 128); hlb_info reports the value in use.
+                          Results do not depend on it. */
   int32_t adjoint;     /* 1: enable hlb_adjoint_run (FP64 storage, pull
                           scheme; its buffers are allocated at the first run);
                           default 0 */

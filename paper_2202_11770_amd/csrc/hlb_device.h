@@ -121,6 +121,13 @@ __device__ inline void st(_Float16 *p, float v) {
   __builtin_nontemporal_store(static_cast<_Float16>(v), p);  // round to nearest even
 }
 __device__ inline uint8_t ld_stream(const uint8_t *p) { return __builtin_nontemporal_load(p); }
+// Population stores of a step: non-temporal, but cached while the two buffers
+// stay in the Infinity Cache between the steps (see in_cache).
+template <bool CACHED, typename T, typename C>
+__device__ inline void st_step(T *p, C v) {
+  if constexpr (CACHED) *p = static_cast<T>(v);  // round to nearest even
+  else st(p, v);
+}
 // Cached stores, for the push scatter: its 64-element runs start anywhere, so
 // neighbouring wavefronts complete each other's lines in L2 (non-temporal
 // stores there measured 13-31% slower).

@@ -67,7 +67,7 @@ constexpr bool kStepShortRows = sizeof(T) == 2;
 // coalesced); the two sites' table loads and 36 gathers are all issued
 // before either collides, which doubles the bytes a wavefront has in flight.
 // nb_bulk then counts block pairs.  Only the full step (blk0 = 0) uses it.
-template <typename T, bool POROUS, bool NARROW, int SPT = 1>
+template <typename T, bool POROUS, bool NARROW, bool CACHED, int SPT = 1>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T, SPT, NARROW>, 8))) void k_step(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
     int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots,
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
       int32_t ps = (int32_t)p;
       asm volatile("" : "+v"(ps));
 #pragma unroll
-      for (int i = 0; i < Q; ++i) st(at<NARROW>(B, ps, i), g[i]);
+      for (int i = 0; i < Q; ++i) st_step<CACHED>(at<NARROW>(B, ps, i), g[i]);
     } else {
       flux = 0;
     }
@@ -114,10 +114,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
         using N = Narrow<T>;
         const uint32_t own = N::voff(((uint32_t)p << N::S) + N::D);
 #pragma unroll
-        for (int i = 0; i < Q; ++i) st(N::at(B, i, own), g[i]);
+        for (int i = 0; i < Q; ++i) st_step<CACHED>(N::at(B, i, own), g[i]);
       } else {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p, i), g[i]);
+        for (int i = 0; i < Q; ++i) st_step<CACHED>(at<NARROW>(B, (int32_t)p, i), g[i]);
       }
     }
     if constexpr (POROUS) add_flux(flux_slots, double(flux));
@@ -137,9 +137,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
       collide<SH>(g, omega, C(a.rho0));
       collide<SH>(h, omega, C(a.rho0));
 #pragma unroll
-      for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p, i), g[i]);
+      for (int i = 0; i < Q; ++i) st_step<CACHED>(at<NARROW>(B, (int32_t)p, i), g[i]);
 #pragma unroll
-      for (int i = 0; i < Q; ++i) st(at<NARROW>(B, (int32_t)p2, i), h[i]);
+      for (int i = 0; i < Q; ++i) st_step<CACHED>(at<NARROW>(B, (int32_t)p2, i), h[i]);
     }
     if constexpr (POROUS) add_flux(flux_slots, double(flux));
   }
@@ -442,7 +442,7 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
   const unsigned grid = (unsigned)(nb_io + nb_launch);
   hipError_t er;
   if (e0 && (er = hipEventRecord(e0, s)) != hipSuccess) return er;
-  const bool narrow = use_narrow<T>(L);
+  const bool narrow = use_narrow<T>(L), cached = in_cache(L.np, sizeof(T));
   uint32_t *done = reinterpret_cast<uint32_t *>(d.acc + 3);
   if (grid > 0) {
 #define HLB_STEP(P, N)                                                                                    \
@@ -451,11 +451,14 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
       k_step_push<T, P, N><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk,          \
                                                    cfg.xcd_chunk, omega, d.flux, done);                        \
     else if (pair)                                                                                      \
-      k_step<T, P, N, 2><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, 0, nb_launch,             \
-                                                 cfg.xcd_chunk, omega, d.flux, done);                          \
+      k_step<T, P, N, false, 2><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, 0, nb_launch,      \
+                                                        cfg.xcd_chunk, omega, d.flux, done);            \
+    else if (cached)                                                                                    \
+      k_step<T, P, N, true><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk,         \
+                                                    cfg.xcd_chunk, omega, d.flux, done);                \
     else                                                                                                \
-      k_step<T, P, N><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk, cfg.xcd_chunk, \
-                                              omega, d.flux, done);                                            \
+      k_step<T, P, N, false><<<grid, kBlock, 0, s>>>(A, B, a, d.order, n0, nb_io, blk0, nb_bulk,        \
+                                                     cfg.xcd_chunk, omega, d.flux, done);               \
   } while (0)
     if (cfg.porous) {
       if (narrow) HLB_STEP(true, kStepNarrow<T>);

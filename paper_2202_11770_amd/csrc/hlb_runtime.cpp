@@ -63,11 +63,15 @@ size_t storage_bytes(int storage) {
 
 // Workgroup-to-XCD chunk of the step kernel when the caller leaves it to
 // the library (hlb_options.xcd_remap = -1), from sweeps of the chunk (0 to
-// 4096 blocks) on the 2e7- and 2e8-site trees: FP16 runs fastest in plain
+// 4096 blocks).  While both buffers stay in the Infinity Cache: 32 blocks in every
+// storage (203,352-site tree, FP64 14.5 us a step with 64 and 13.6 with 32; 414,834
+// sites, FP32 16.2 with 8 and 15.5, FP16 11.35 with 0 and 10.6; equal within 1% elsewhere).
+// Beyond it, on the 2e7- and 2e8-site trees: FP16 runs fastest in plain
 // block order at both sizes; FP64 with 64 blocks per chunk while a
 // population buffer fits in 4 GiB and 256 above; FP32 with 8 and 128.
 int auto_xcd_chunk(int storage, int64_t np) {
   const bool big = (uint64_t)Q * (uint64_t)np * storage_bytes(storage) > (uint64_t(1) << 32);
+  if (buffers_mb(np, storage_bytes(storage)) <= kCacheMB) return 32;
   if (storage == HLB_F16_SHIFTED) return 0;
   if (storage == HLB_F32_SHIFTED) return big ? 128 : 8;
   return big ? 256 : 64;
