@@ -322,8 +322,9 @@ __device__ inline void bulk_offsets(const GatherArgs &a, int64_t p, int64_t blk,
 // load, with p's row index fetched beside it; else from the last position's
 // index, behind p's.  The short chain of loads takes FP16, whose blocks are the
 // shortest, from 140.2 to 138.3 us on the 7.8e6-site tree (against its rows
-// loaded per wavefront); FP64 and FP32 run 0.4% and 1.3% slower with it on the
-// 2.0e7-site tree (1036 to 1040 us, 554 to 562), and as fast on small ones.
+// loaded per wavefront), and FP64 and FP32 while the state stays in the Infinity
+// Cache from 23.4 to 22.6 and 15.5 to 14.6 us (414,834 sites); from HBM those run 0.4%
+// and 1.3% slower with it (2.0e7-site tree, 1036 to 1040 us, 554 to 562).
 template <bool SHORT>
 __device__ inline const int4 *stage_rows(const GatherArgs &a, int64_t blk, int64_t p, int64_t n0, int4 *lrows) {
   int32_t k_row, n4;

@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
     const int64_t blk = blk0 + block_id(b - nb_io, nb_bulk, xcd_chunk);
     const int64_t p = blk * kBlock + threadIdx.x;
     __shared__ int4 lrows[kSegBlock * (kSegRow / 4)];
-    const int4 *lrow = stage_rows<kStepShortRows<T>>(a, blk, p, n0, lrows);
+    const int4 *lrow = stage_rows<kStepShortRows<T> || CACHED>(a, blk, p, n0, lrows);
     if (p < n0) {
       C g[Q];
       flux = gather<false, POROUS, SH, NARROW, true>(A, p, blk, a, g, nullptr, lrow);
