@@ -36,23 +36,20 @@ using namespace dev;
 // group's 256-position blocks blk0, blk0+1, ...  (a split step launches the
 // edge blocks and the rest separately).  Every block, hence every wavefront,
 // runs one group's code path only.
-// Per storage type, measured on the 2e7-site tree: the minimum waves per
-// SIMD the step kernel is compiled for, and whether population addresses use 32-bit byte
-// offsets when a buffer allows it (see at()).  FP64: the natural 4 waves and
-// 32-bit offsets; FP32: 6 waves and 64-bit addresses (32-bit offsets
-// measured 3% slower); FP16: 6 waves and 32-bit offsets.  Measured again
-// with the per-storage workgroup-to-XCD chunk on the 2e7- and 2e8-site
-// trees: FP64 4 waves (5, 6 slower by 0.5-1% on the 2e8 tree).  FP16, with the
-// segment rows in LDS: 7 waves (20 bytes of scratch in the iolet path) 320.7 us
-// on the 2.0e7-site tree, 6 323.1, 8 322.2, 5 334.  FP32, with the segment rows in LDS
-// and the banded order: 6 waves against its natural 5 gave +0.2-0.3% on the
-// trees and +0.9-1.0% on the 6e8-site forest; 4 waves cost 5%.
+// The minimum waves per SIMD the step kernel is compiled for, per storage
+// type.  FP64: the natural 4 (5 and 6 slower by 0.5-1% on the 2e8-site tree, 5 by 1%
+// on the 2e7-site tree).  FP16: 7 waves (20 bytes of scratch in the iolet path)
+// 320.7 us on the 2.0e7-site tree, 6 323.1, 8 322.2, 5 334.  FP32: 6 (5 slower by
+// 0.2-0.3% on the trees and 0.9-1.0% on the 6e8-site forest, 7 by 1%, 4 by 5%).
+// Population addresses are 32-bit byte offsets where a buffer allows it (see
+// at()).  FP32, which once was slower with them, runs faster in every size since the
+// iolet path spills no more and the rows are in LDS: 7.1 to 6.7 us a step of the
+// 125,400-site vessel, 91.5 to 89.3 at 2.95e6 sites, 223.3 to 220.6 at 7.8e6, 553 to 552 at
+// 2.0e7.
 // SPT = 2 (two bulk+wall sites per thread, see below) needs about twice the
 // registers of the bulk path: 4 waves.
 template <typename T, int SPT = 1, bool NARROW = true>
 constexpr int kStepWaves = SPT == 2 ? 4 : (std::is_same<T, double>::value ? 4 : sizeof(T) == 2 ? 7 : 6);
-template <typename T>
-constexpr bool kStepNarrow = !std::is_same<T, float>::value;
 // The bulk path of a full step stages each block's segment rows through LDS
 // (stage_rows): FP64 and FP32 +0.4% on the 2e7- and +0.5-1.3% on the 2e8-site
 // tree against five row loads per lane, each of which touches a cache line per
@@ -417,7 +414,7 @@ inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBl
 // bias of the bulk path's addressing (Narrow).
 template <typename T>
 bool use_narrow(const Layout &L) {
-  return kStepNarrow<T> && (uint64_t)Q * (uint64_t)L.np * sizeof(T) + Narrow<T>::BIAS <= (uint64_t(1) << 32);
+  return (uint64_t)Q * (uint64_t)L.np * sizeof(T) + Narrow<T>::BIAS <= (uint64_t(1) << 32);
 }
 
 template <typename T>
@@ -461,10 +458,10 @@ hipError_t step_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, in
                                                      cfg.xcd_chunk, omega, d.flux, done);               \
   } while (0)
     if (cfg.porous) {
-      if (narrow) HLB_STEP(true, kStepNarrow<T>);
+      if (narrow) HLB_STEP(true, true);
       else HLB_STEP(true, false);
     } else {
-      if (narrow) HLB_STEP(false, kStepNarrow<T>);
+      if (narrow) HLB_STEP(false, true);
       else HLB_STEP(false, false);
     }
 #undef HLB_STEP
@@ -528,10 +525,10 @@ hipError_t macros_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, 
                                                        direct ? 1 : 0, cfg.tau, rho, u, wss, f_out);                 \
   } while (0)
   if (cfg.porous) {
-    if (narrow) HLB_MACROS(true, kStepNarrow<T>);
+    if (narrow) HLB_MACROS(true, true);
     else HLB_MACROS(true, false);
   } else {
-    if (narrow) HLB_MACROS(false, kStepNarrow<T>);
+    if (narrow) HLB_MACROS(false, true);
     else HLB_MACROS(false, false);
   }
 #undef HLB_MACROS
