@@ -141,7 +141,7 @@ struct GatheredMoments {
 // per site and the pull table, where separate collide and stream kernels
 // moved mu through memory in between (814 B).  Reverse step of the 2.95e6-site
 // tree, k_adj_iolet included: 496 -> 261 us outside the objective window, 577
-// -> 284 inside it; with porosity 643 -> 277 and 734 -> 291.
+// -> 279 inside it; with porosity 643 -> 275 and 734 -> 285.
 //
 // The porosity derivative: at a wall link j the reflected value is
 // s_{t-1}(p, opp(j)), so with h_j = w_j rho0 - s_{t-1}(p, opp(j)) and
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAdjWave
   const int64_t p = blk * kBlock + threadIdx.x;
   // bulk+wall blocks (block-uniform): the segment rows through LDS
   __shared__ int4 lrows[kSegBlock * (kSegRow / 4)];
-  const int4 *lrow = bulk ? stage_rows<false>(a, blk, p, A.n0, lrows) : nullptr;
+  const int4 *lrow = bulk ? stage_rows<true>(a, blk, p, A.n0, lrows) : nullptr;
   double jsum = 0.0;
   if (!bulk || p < A.n0) {
     const int32_t p32 = (int32_t)p;

@@ -324,7 +324,9 @@ __device__ inline void bulk_offsets(const GatherArgs &a, int64_t p, int64_t blk,
 // shortest, from 140.2 to 138.3 us on the 7.8e6-site tree (against its rows
 // loaded per wavefront), and FP64 and FP32 while the state stays in the Infinity
 // Cache from 23.4 to 22.6 and 15.5 to 14.6 us (414,834 sites); from HBM those run 0.4%
-// and 1.3% slower with it (2.0e7-site tree, 1036 to 1040 us, 554 to 562).
+// and 1.3% slower with it (2.0e7-site tree, 1036 to 1040 us, 554 to 562).  The
+// adjoint's step takes it too (2.95e6-site tree, 286 to 279 us inside the objective
+// window, 262 to 261 outside).
 template <bool SHORT>
 __device__ inline const int4 *stage_rows(const GatherArgs &a, int64_t blk, int64_t p, int64_t n0, int4 *lrows) {
   int32_t k_row, n4;
