@@ -191,14 +191,14 @@ struct WkFlux {
       k = kk;
       q += v;
     } else {
-      add_done(acc + (int64_t)kk * stride, v);
+      add_device(acc + (int64_t)kk * stride, v);
     }
   }
-  // An atomic whose result is waited for: it has been performed, for every
-  // block of the device, when this returns (see finish_outlets).
-  __device__ static void add_done(double *p, double v) {
-    const double old = __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("" ::"v"(old) : "memory");
+  // Not waited for (see finish_outlets): with its result awaited, every
+  // further outlet of a wavefront was one more round trip (50 steps of the
+  // 203,352-site tree alone 854 us, without 814).
+  __device__ static void add_device(double *p, double v) {
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 };
 
@@ -214,7 +214,7 @@ __device__ inline void wave_add_grouped(double *acc, const WkFlux &w, int64_t st
     const int kl = __shfl(w.k, leader, 64);
     const bool mine = pending && w.k == kl;
     const double s = wave_sum(mine ? w.q : 0.0);
-    if ((int)(threadIdx.x & 63) == leader) WkFlux::add_done(acc + (int64_t)kl * stride, s);
+    if ((int)(threadIdx.x & 63) == leader) WkFlux::add_device(acc + (int64_t)kl * stride, s);
     if (mine) pending = false;
   }
 }
@@ -397,12 +397,14 @@ __device__ inline void windkessel(const GatherArgs &a, int k, int64_t t, double 
 // 203,352-site tree with 16 outlets takes 19.0 us instead of 20.0, one among
 // other simulations' steps 11.5 instead of 12.5.
 // The outflow and the count are only touched by atomics of device scope, each
-// block's outflow atomics have returned before its barrier, and the count
-// follows the barrier: no fence is needed, and none is wanted -- one of device
+// wavefront waits for its outflow atomics (vmcnt counts them until they are
+// performed) before the block's barrier, and the count follows the barrier:
+// no fence is needed, and none is wanted -- one of device
 // scope writes back and drops the XCD's L2 under the bulk blocks (with two of
 // them that step took 21.1 us).
 __device__ inline void finish_outlets(const GatherArgs &a, int64_t nb_io, uint32_t *done) {
   __shared__ bool last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0)
     last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)nb_io - 1u;
