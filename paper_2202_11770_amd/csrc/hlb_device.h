@@ -251,6 +251,41 @@ __device__ inline C s_eq(int i, C dr, C rho, C ux, C uy, C uz, C usq15) {
   return SH ? wgt<C>(i) * (dr + rho * q) : wgt<C>(i) * rho * (C(1) + q);
 }
 
+// The ghost density's fill (pressure iolets): the equilibrium at density rho
+// and the velocity g = (u.n) n.  Every multiply-add is written out, so that
+// the fill rounds alike in every kernel that forms it, whatever code stands
+// around it.  Left to the compiler, one arrangement fused the x product into
+// c.g of directions 7 and 9 and another the y product, and the FP32 and FP16
+// fields of vessels with oblique outlets moved by that rounding.
+template <typename C>
+struct GhostVelocity {
+  C un, nx, ny, nz, gx, gy, gz, sq;
+  __device__ GhostVelocity(C ux, C uy, C uz, const double (&n)[3]) : nx(C(n[0])), ny(C(n[1])), nz(C(n[2])) {
+#pragma clang fp contract(off)
+    un = fused(uz, nz, fused(ux, nx, uy * ny));
+    gx = un * nx;
+    gy = un * ny;
+    gz = un * nz;
+    sq = fused(gz, gz, fused(gx, gx, gy * gy));
+  }
+  __device__ static double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+  __device__ static float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+  // s_eq along direction i, dr = rho - rho0
+  template <bool SH>
+  __device__ C fill(int i, C dr, C rho) const {
+#pragma clang fp contract(off)
+    const C ex = C(cx(i)), ey = C(cy(i)), ez = C(cz(i));
+    C cu;  // c.g: x and y, one product fused (x, unless y alone is positive), then z fused
+    if (cx(i) && cy(i))
+      cu = cx(i) < 0 && cy(i) > 0 ? fused(ny, un, -gx) : fused(ex * nx, un, ey * gy);
+    else
+      cu = cx(i) ? fused(ey, gy, ex * gx) : fused(ex, gx, ey * gy);
+    cu = cz(i) ? fused(ez * nz, un, cu) : fused(ez, gz, cu);
+    const C q = fused(C(-1.5), sq, fused(C(3), cu, (C(4.5) * cu) * cu));
+    return SH ? wgt<C>(i) * fused(q, rho, dr) : (wgt<C>(i) * rho) * (C(1) + q);
+  }
+};
+
 // BGK collision, eq. (3a) with dt = 1: s' = s + omega (s_eq - s).
 template <bool SH, typename C>
 __device__ inline void collide(C (&s)[Q], C omega, C rho0) {
@@ -545,13 +580,11 @@ __device__ inline C gather_iolet(const T *__restrict__ A, int64_t p, const Gathe
         __builtin_amdgcn_sched_barrier(0);
       }
     } else {
-      const C un = ux * C(K.n[0]) + uy * C(K.n[1]) + uz * C(K.n[2]);
-      const C gx = un * C(K.n[0]), gy = un * C(K.n[1]), gz = un * C(K.n[2]);
-      const C uu = C(1.5) * (gx * gx + gy * gy + gz * gz);
+      const GhostVelocity<C> ghost(ux, uy, uz, K.n);
 #pragma unroll
       for (int i = 1; i < Q; ++i) {
         const bool mine = (io.links >> i) & 1u;
-        const C v = s_eq<SH>(i, C(val - a.rho0), C(val), gx, gy, gz, uu);
+        const C v = ghost.template fill<SH>(i, C(val - a.rho0), C(val));
         flux += mine ? v - g[i] : C(0);
         out += mine ? double(g[i] - v) : 0.0;
         g[i] = mine ? v : g[i];
@@ -750,10 +783,7 @@ __device__ inline C scatter(T *__restrict__ B, int64_t p, int64_t blk, const Gat
         if (K.kind == HLB_IOLET_VELOCITY) {
           v = back + C(a.corr[(int64_t)(i - 1) * a.nio + (p - a.io_begin)] * val * ladd_scale);
         } else {
-          const C un = ux * C(K.n[0]) + uy * C(K.n[1]) + uz * C(K.n[2]);
-          const C gx = un * C(K.n[0]), gy = un * C(K.n[1]), gz = un * C(K.n[2]);
-          const C uu = C(1.5) * (gx * gx + gy * gy + gz * gz);
-          v = s_eq<SH>(i, C(val - a.rho0), C(val), gx, gy, gz, uu);
+          v = GhostVelocity<C>(ux, uy, uz, K.n).template fill<SH>(i, C(val - a.rho0), C(val));
         }
         if (K.wk && a.io_flux) wkf->add(a.io_flux, k, double(back - v));
       }
