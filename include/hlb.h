@@ -143,16 +143,12 @@ typedef struct {
   int32_t graph_steps; /* k > 0 (even, up to 4096): hlb_step replays a
                           captured HIP graph of k steps for as many whole
                           graphs as fit and launches the rest one by one;
-                          0 (default): left to the library: on the context's
-                          own stream, a call repeated with the same count
-                          and unchanged settings is replayed as one graph
-                          where that pays, every other step is its own
-                          launch.  A graph is recaptured when a buffer, table
-                          pointer, porosity or Windkessel setting changes;
-                          it is not used while timing is on.  Results do not
-                          depend on it (bit for bit, except where atomics
-                          already make the Windkessel outflow
-                          order-dependent). */
+                          0 (default): every step is its own launch.  A
+                          graph is recaptured when a buffer, table pointer,
+                          porosity or Windkessel setting changes; it is not
+                          used while timing is on.  Results do not depend on
+                          it (bit for bit, except where atomics already make
+                          the Windkessel outflow order-dependent). */
   int32_t order_block; /* log2 of the band / column width of
                           HLB_ORDER_BANDS and HLB_ORDER_COLUMNS, 1..16
                           (default 7); ignored by the other orders */
@@ -300,7 +296,7 @@ typedef struct {
   int32_t porous;           /* a porosity field is set */
   int32_t scheme;           /* hlb_scheme of the context */
   int32_t sites_per_thread; /* bulk+wall sites per thread of the full pull step */
-  int32_t graph_steps;      /* hlb_options.graph_steps */
+  int32_t graph_steps;      /* steps per replayed graph in hlb_step (0: none) */
   int32_t xcd_remap;        /* workgroup-to-XCD chunk in use (hlb_options.xcd_remap) */
 } hlb_info_t;
 hlb_status hlb_info(const hlb_ctx *ctx, hlb_info_t *info);

@@ -249,13 +249,7 @@ struct hlb_ctx {
   int64_t adj_wk_nslots = 0;
   // replayed step graphs (hlb_step): one per starting buffer, captured with
   // the time read from t_dev
-  int graph_steps = 0;            // steps per graph asked for; 0: left to the library (auto_graph)
-  int64_t graph_len = 0;          // steps of the captured graphs
-  // calls of hlb_step in a row with the same count and the same launches
-  int64_t auto_n = 0, auto_calls = 0;
-  DevPtrs auto_d;
-  LaunchCfg auto_cfg;
-  bool auto_off = false;          // a capture failed: plain launches from then on
+  int graph_steps = 0;            // steps per graph; 0: no graphs
   int64_t *t_dev = nullptr;       // [1] time at the start of the next replay
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -1298,11 +1292,11 @@ static void macro_source(const hlb_ctx *c, int *src, bool *direct) {
 
 namespace {
 
-// Capture the graph of `len` steps that starts from buffer `cur`:
+// Capture the graph of c->graph_steps steps that starts from buffer `cur`:
 // step k reads the time as *t_dev + k, and a last node advances *t_dev, so
 // that back-to-back replays continue the count.  Captured on a private
 // stream (the context stream may be the null stream, which cannot capture).
-hlb_status capture_steps(hlb_ctx *c, int cur, int64_t len) {
+hlb_status capture_steps(hlb_ctx *c, int cur) {
   if (!c->t_dev) {
     void *p = nullptr;
     if (hlb_status st = dev_alloc(c, &p, sizeof(int64_t))) return st;
@@ -1313,27 +1307,24 @@ hlb_status capture_steps(hlb_ctx *c, int cur, int64_t len) {
   d.t_base = c->t_dev;
   HIP_TRY(hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
-  for (int64_t k = 0; k < len && e == hipSuccess; ++k)
-    e = launch_step(c->cfg, c->L, d, (int)((cur + k) & 1), k, c->cap_stream, nullptr, nullptr);
-  if (e == hipSuccess) e = launch_add_time(c->t_dev, len, c->cap_stream);
+  for (int k = 0; k < c->graph_steps && e == hipSuccess; ++k)
+    e = launch_step(c->cfg, c->L, d, (cur + k) & 1, k, c->cap_stream, nullptr, nullptr);
+  if (e == hipSuccess) e = launch_add_time(c->t_dev, c->graph_steps, c->cap_stream);
   hipGraph_t g = nullptr;
   const hipError_t e2 = hipStreamEndCapture(c->cap_stream, &g);
   if (e == hipSuccess) e = e2;
   if (e == hipSuccess) e = hipGraphInstantiate(&c->graph[cur], g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
   if (e != hipSuccess) {
-    (void)hipGetLastError();
     c->graph[cur] = nullptr;
     return fail(HLB_EDEVICE, "capturing the step graph: %s", hipGetErrorString(e));
   }
   return HLB_OK;
 }
 
-// reps replays of graphs of `len` steps from the current time and buffer.
-// Nothing has been launched if it fails with `*launched` false.
-hlb_status replay_steps(hlb_ctx *c, int64_t reps, int64_t len, bool *launched) {
-  *launched = false;
-  if (c->graph_len != len || !same_launch(c->graph_d, c->d) || !same_launch(c->graph_cfg, c->cfg)) {
+// reps replays of the step graph from the current time and buffer.
+hlb_status replay_steps(hlb_ctx *c, int64_t reps) {
+  if (!same_launch(c->graph_d, c->d) || !same_launch(c->graph_cfg, c->cfg)) {
     HIP_TRY(hipStreamSynchronize(c->stream));
     for (auto &g : c->graph)
       if (g) {
@@ -1342,46 +1333,15 @@ hlb_status replay_steps(hlb_ctx *c, int64_t reps, int64_t len, bool *launched) {
       }
     c->graph_d = c->d;
     c->graph_cfg = c->cfg;
-    c->graph_len = len;
   }
-  // the starting buffers of this call's replays (they alternate for an odd len)
-  for (int k = 0; k < ((len & 1) && reps > 1 ? 2 : 1); ++k)
-    if (!c->graph[c->cur ^ k])
-      if (hlb_status st = capture_steps(c, c->cur ^ k, len)) return st;
-  *launched = true;
+  if (!c->graph[c->cur])
+    if (hlb_status st = capture_steps(c, c->cur)) return st;
   HIP_TRY(launch_set_time(c->t_dev, c->t, c->stream));
-  for (int64_t r = 0; r < reps; ++r) {
-    HIP_TRY(hipGraphLaunch(c->graph[c->cur], c->stream));
-    c->cur = (int)((c->cur + len) & 1);
-    c->direct = false;
-    c->t += len;
-  }
+  for (int64_t r = 0; r < reps; ++r) HIP_TRY(hipGraphLaunch(c->graph[c->cur], c->stream));
+  // an even number of steps per graph: the state is back in buffer cur
+  c->direct = false;
+  c->t += reps * c->graph_steps;
   return HLB_OK;
-}
-
-// Whether a call of n steps is replayed as one graph although no graph length
-// was asked for.  The context's own stream keeps order with the legacy null
-// stream, for which the runtime adds a barrier to every single launch while
-// the null stream has work in flight (a program's torch operations between the
-// calls): 6 us a step.  A graph is one launch: 100 FP32 steps of the 125,400-site vessel
-// with its fields converted by torch 1450 -> 915 us, 40 porous steps of the
-// 1.1e6-site tree 1920 -> 1718, 50 FP16 steps of the 7.8e6-site tree 7530 -> 7240.
-// With the null stream idle a graph costs 10 to 25 us, so only calls of
-// some 400 us and more take one; and its capture costs about as much as the call,
-// so only the fifth and later of calls in a row with the same count and
-// unchanged buffers, tables and options do.  Never on a caller's stream, which may be captured
-// itself and has no such barriers.
-bool auto_graph(hlb_ctx *c, int64_t n) {
-  if (c->graph_steps != 0 || c->auto_off || c->stream != c->own_stream || n < 8 || n > 1024) return false;
-  const double us = (double)n * (6.0 + 2.0 * (double)buf_bytes(c) / 6e6);
-  if (us < 400.0) return false;
-  if (n != c->auto_n || !same_launch(c->auto_d, c->d) || !same_launch(c->auto_cfg, c->cfg)) {
-    c->auto_n = n;
-    c->auto_calls = 0;
-    c->auto_d = c->d;
-    c->auto_cfg = c->cfg;
-  }
-  return ++c->auto_calls > 4;
 }
 
 }  // namespace
@@ -1393,15 +1353,8 @@ hlb_status hlb_step(hlb_ctx *c, int64_t n) {
   if (hlb_status st = bind(c)) return st;
   if (c->graph_steps > 0 && !c->timing && n >= c->graph_steps) {
     const int64_t reps = n / c->graph_steps;
-    bool launched;
-    if (hlb_status st = replay_steps(c, reps, c->graph_steps, &launched)) return st;
+    if (hlb_status st = replay_steps(c, reps)) return st;
     n -= reps * c->graph_steps;
-  } else if (!c->timing && auto_graph(c, n)) {
-    bool launched;
-    const hlb_status st = replay_steps(c, 1, n, &launched);
-    if (!st || launched) return st;
-    c->auto_off = true;  // no memory or no capture: the steps are launched one by one
-    g_err.clear();
   }
   for (int64_t s = 0; s < n; ++s) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
