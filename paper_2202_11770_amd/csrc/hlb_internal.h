@@ -89,7 +89,8 @@ struct DevPtrs {
   double *tables = nullptr;         // concatenated per-step iolet tables
   double *phi = nullptr;            // [np] porosity, or null
   double *acc = nullptr;            // [4]: boundary flux since t0 up to the last fold; ...; [3] the
-                                    // step kernel's count of finished iolet blocks (zero between launches)
+                                    // step kernel's count of finished iolet blocks (zero between launches;
+                                    // never saved or restored)
   double *flux = nullptr;           // [kFluxSlots] boundary flux since the last fold (see kFluxSlots);
                                     // the tail of the allocation of `partial`
   double *partial = nullptr;        // [partial_len] reduction scratch

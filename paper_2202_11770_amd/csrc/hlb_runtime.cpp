@@ -1584,7 +1584,7 @@ hlb_status hlb_snapshot_save(hlb_ctx *c, int32_t slot) {
   HIP_TRY(hipMemcpyAsync(s.f[0], c->d.f[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(s.f[1], c->d.f[1], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
-  HIP_TRY(hipMemcpyAsync(s.acc, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(hipMemcpyAsync(s.acc, c->d.acc, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   s.t = c->t; s.t0 = c->t0; s.m0 = c->m0; s.cur = c->cur; s.direct = c->direct; s.valid = true;
   return HLB_OK;
 }
@@ -1597,7 +1597,7 @@ hlb_status hlb_snapshot_restore(hlb_ctx *c, int32_t slot) {
   if (hlb_status st = bind(c)) return st;
   HIP_TRY(hipMemcpyAsync(c->d.f[0], s.f[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.f[1], s.f[1], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->d.acc, s.acc, 4 * sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(hipMemcpyAsync(c->d.acc, s.acc, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
   c->t = s.t; c->t0 = s.t0; c->m0 = s.m0; c->cur = s.cur; c->direct = s.direct;
   return HLB_OK;
@@ -1609,7 +1609,7 @@ struct StateHeader {
   int64_t n_sites, np, t, t0;
   int32_t storage, cur, direct, scheme;
   double m0;
-  double acc[4];
+  double acc[4];  // [0] the boundary flux; the others are written as zero and not read
 };
 }  // namespace
 
@@ -1630,7 +1630,7 @@ hlb_status hlb_state_save(hlb_ctx *c, void *buf) {
   h.storage = c->cfg.storage; h.cur = c->cur; h.direct = c->direct ? 1 : 0; h.m0 = c->m0;
   h.scheme = c->cfg.scheme;
   HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
-  HIP_TRY(hipMemcpyAsync(h.acc, c->d.acc, 4 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(hipMemcpyAsync(h.acc, c->d.acc, sizeof(double), hipMemcpyDeviceToHost, c->stream));
   char *b = static_cast<char *>(buf);
   HIP_TRY(hipMemcpyAsync(b + sizeof(h), c->d.f[0], buf_bytes(c), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipMemcpyAsync(b + sizeof(h) + buf_bytes(c), c->d.f[1], buf_bytes(c), hipMemcpyDeviceToHost, c->stream));
@@ -1651,7 +1651,7 @@ hlb_status hlb_state_load(hlb_ctx *c, const void *buf) {
   const char *b = static_cast<const char *>(buf);
   HIP_TRY(hipMemcpyAsync(c->d.f[0], b + sizeof(h), buf_bytes(c), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.f[1], b + sizeof(h) + buf_bytes(c), buf_bytes(c), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->d.acc, h.acc, 4 * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(hipMemcpyAsync(c->d.acc, h.acc, sizeof(double), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->t = h.t; c->t0 = h.t0; c->m0 = h.m0; c->cur = h.cur; c->direct = h.direct != 0;
