@@ -48,8 +48,13 @@ using namespace dev;
 // 2.0e7.
 // SPT = 2 (two bulk+wall sites per thread, see below) needs about twice the
 // registers of the bulk path: 4 waves.
+// The push step's iolet path keeps more values at once: FP16 takes 6 waves
+// there (28 to 36 bytes of scratch; with 7, 68 to 84, and 10 steps of the
+// 13,312-site pipe take 85.6 us instead of 77.5, of the 1.1e6-site tree 306 instead of 296).
 template <typename T, int SPT = 1, bool NARROW = true>
 constexpr int kStepWaves = SPT == 2 ? 4 : (std::is_same<T, double>::value ? 4 : sizeof(T) == 2 ? 7 : 6);
+template <typename T>
+constexpr int kPushWaves = std::is_same<T, double>::value ? 4 : 6;
 // The bulk path of a full step stages each block's segment rows through LDS
 // (stage_rows): FP64 and FP32 +0.4% on the 2e7- and +0.5-1.3% on the 2e8-site
 // tree against five row loads per lane, each of which touches a cache line per
@@ -147,7 +152,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
 // own 19 values (coalesced), collides and scatters (scatter()).  Same block
 // layout, XCD remap and occupancy as k_step.
 template <typename T, bool POROUS, bool NARROW>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T>, 8))) void k_step_push(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kPushWaves<T>, 8))) void k_step_push(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
     int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots,
     uint32_t *done) {
