@@ -255,23 +255,28 @@ __global__ __launch_bounds__(kBlock) void k_set_state(T *__restrict__ Pre, T *__
 // the kernel runs at 4 waves per SIMD instead of 2: 862 -> 824 us on the 2.0e7-site
 // tree in FP64, 722 -> 556 in FP32, 282 -> 199 on the 7.8e6-site tree in FP16, 8.4 ->
 // 6.7 on the 13,312-site pipe (5 waves spill: 917 us).
-template <typename T, bool POROUS, bool NARROW, bool STATE>
+// SRC: whether A holds pre-collision values, read as they are, or the
+// post-collision values that they are gathered from.
+enum MacroSrc { kDirect, kPulled, kPulledPorous };
+template <typename T, MacroSrc SRC, bool NARROW, bool STATE>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_macros(
     const T *__restrict__ A, GatherArgs a, const int32_t *__restrict__ order, int64_t n0, int64_t nb_io, int64_t nb_bulk,
-    int xcd_chunk, int direct, double tau, double *__restrict__ rho_o, double *__restrict__ u_o,
+    int xcd_chunk, double tau, double *__restrict__ rho_o, double *__restrict__ u_o,
     double *__restrict__ wss_o, double *__restrict__ f_o) {
   const int64_t b = blockIdx.x;
   const bool bulk = b >= nb_io;
   const int64_t blk = bulk ? block_id(b - nb_io, nb_bulk, xcd_chunk) : a.io_begin / kBlock + b;
   const int64_t p = blk * kBlock + threadIdx.x;
   __shared__ int4 lrows[kSegBlock * (kSegRow / 4)];
-  const int4 *lrow = bulk ? stage_rows<kStepShortRows<T>>(a, blk, p, n0, lrows) : nullptr;
+  // values read as they are need the rows for the wall links of the stress alone
+  const int4 *lrow =
+      bulk && (SRC != kDirect || wss_o) ? stage_rows<kStepShortRows<T>>(a, blk, p, n0, lrows) : nullptr;
   if (bulk && p >= n0) return;
   const int32_t id = order[p];
   const int32_t p32 = (int32_t)p;
-  constexpr bool SH = kShifted<T>;
+  constexpr bool SH = kShifted<T>, POROUS = SRC == kPulledPorous;
   double g[Q];
-  if (direct) {
+  if constexpr (SRC == kDirect) {
 #pragma unroll
     for (int i = 0; i < Q; ++i) g[i] = ld(at<NARROW>(A, p32, i));
   } else if (bulk) {
@@ -520,21 +525,24 @@ hipError_t macros_impl(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, 
   const int64_t nb_io = (L.gbeg[kGroups] - L.io_begin) / kBlock;
   const unsigned grid = (unsigned)(nb_io + nb_bulk);
   const bool narrow = use_narrow<T>(L);
-#define HLB_MACROS(P, N)                                                                                             \
-  do {                                                                                                               \
-    if (f_out)                                                                                                       \
-      k_macros<T, P, N, true><<<grid, kBlock, 0, s>>>(A, a, d.order, n0, nb_io, nb_bulk, cfg.xcd_chunk,              \
-                                                      direct ? 1 : 0, cfg.tau, rho, u, wss, f_out);                  \
-    else                                                                                                             \
-      k_macros<T, P, N, false><<<grid, kBlock, 0, s>>>(A, a, d.order, n0, nb_io, nb_bulk, cfg.xcd_chunk,             \
-                                                       direct ? 1 : 0, cfg.tau, rho, u, wss, f_out);                 \
+#define HLB_MACROS(SRC, N)                                                                                       \
+  do {                                                                                                           \
+    if (f_out)                                                                                                   \
+      k_macros<T, SRC, N, true><<<grid, kBlock, 0, s>>>(A, a, d.order, n0, nb_io, nb_bulk, cfg.xcd_chunk,        \
+                                                        cfg.tau, rho, u, wss, f_out);                            \
+    else                                                                                                         \
+      k_macros<T, SRC, N, false><<<grid, kBlock, 0, s>>>(A, a, d.order, n0, nb_io, nb_bulk, cfg.xcd_chunk,       \
+                                                         cfg.tau, rho, u, wss, f_out);                           \
   } while (0)
-  if (cfg.porous) {
-    if (narrow) HLB_MACROS(true, true);
-    else HLB_MACROS(true, false);
+  if (direct) {
+    if (narrow) HLB_MACROS(kDirect, true);
+    else HLB_MACROS(kDirect, false);
+  } else if (cfg.porous) {
+    if (narrow) HLB_MACROS(kPulledPorous, true);
+    else HLB_MACROS(kPulledPorous, false);
   } else {
-    if (narrow) HLB_MACROS(false, true);
-    else HLB_MACROS(false, false);
+    if (narrow) HLB_MACROS(kPulled, true);
+    else HLB_MACROS(kPulled, false);
   }
 #undef HLB_MACROS
   return hipGetLastError();
