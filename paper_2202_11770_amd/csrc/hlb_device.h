@@ -164,20 +164,27 @@ __device__ inline void add_flux(double *flux, double v) {
     atomicAdd(flux + (((uint32_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) & (kFluxSlots - 1)), s);
 }
 
-// The sum of the partial sums, in the same order wherever it is formed: every
-// thread of a kBlock-thread workgroup calls it; the value is thread 0's.
-__device__ inline double sum_flux(const double *flux, double *red) {
-  double s = 0.0;
-#pragma unroll 4
-  for (int k = threadIdx.x; k < kFluxSlots; k += kBlock) s += flux[k];
-  s = wave_sum(s);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+// The sum of a kBlock-thread workgroup's values; every thread calls it, the
+// value is thread 0's.  red: kBlock / 64 doubles, another run for each call.
+__device__ inline double block_sum(double v, double *red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double b = 0.0;
   if (threadIdx.x == 0)
     for (int w = 0; w < kBlock / 64; ++w) b += red[w];
   return b;
+}
+
+// This thread's share of the flux's partial sums, all loads in flight: the
+// boundary flux is acc[0] + block_sum of the shares, in the same order
+// wherever it is formed.
+__device__ inline double flux_share(const double *flux) {
+  static_assert(kFluxSlots % kBlock == 0, "whole rounds");
+  double s = 0.0;
+#pragma unroll
+  for (int k = 0; k < kFluxSlots / kBlock; ++k) s += flux[threadIdx.x + k * kBlock];
+  return s;
 }
 
 // Per-site outflow of a Windkessel outlet (k < 0: none), gathered while the

@@ -39,7 +39,7 @@ constexpr int64_t kPopTile = int64_t(1) << kPopTileShift;
 // kFluxSlots partial sums (wavefront index mod kFluxSlots): with porous walls
 // nearly every wavefront has a share, and one address takes them one after
 // the other (12 ns each: the FP32 step of a 1.1e6-site tree took 226 us, and
-// takes 54 us with the sums spread and porous_walls() after the gathers).  The sums are folded into DevPtrs::acc[0] before that is read.
+// takes 54 us with the sums spread and porous_walls() after the gathers).
 constexpr int kFluxSlots = 4096;
 // Partial sums of the mass reduction (one per workgroup, at most).
 constexpr int64_t kMassPartials = 4095;
@@ -88,11 +88,11 @@ struct DevPtrs {
   IoletDev *io = nullptr;           // [n_iolets]
   double *tables = nullptr;         // concatenated per-step iolet tables
   double *phi = nullptr;            // [np] porosity, or null
-  double *acc = nullptr;            // [4]: boundary flux since t0 up to the last fold; ...; [3] the
-                                    // step kernel's count of finished iolet blocks (zero between launches;
-                                    // never saved or restored)
-  double *flux = nullptr;           // [kFluxSlots] boundary flux since the last fold (see kFluxSlots);
-                                    // the tail of the allocation of `partial`
+  double *acc = nullptr;            // [4]: [0] boundary flux from t0 to the last restored state; [1] the total
+                                    // last formed; [3] the step kernel's count of finished iolet blocks
+                                    // (zero between launches; never saved or restored)
+  double *flux = nullptr;           // [kFluxSlots] boundary flux since then (see kFluxSlots); the tail of
+                                    // the allocation of `partial`
   double *partial = nullptr;        // [partial_len] reduction scratch
   int64_t partial_len = 0;
   double *io_scratch = nullptr;     // [np*19] host-exchange staging (allocated lazily)
@@ -165,15 +165,19 @@ hipError_t launch_macros(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d
 // buffer `pre` := f - w rho0, buffer 1-pre := its collision.
 hipError_t launch_set_state(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, int pre,
                             const double *staging, hipStream_t s);
-// acc[0] += the sum of the partial sums flux[0..kFluxSlots), which are cleared.
-hipError_t launch_fold_flux(double *acc, double *flux, hipStream_t s);
+// *out := the boundary flux, acc[0] + the sum of flux[0..kFluxSlots).
+hipError_t launch_total_flux(const double *acc, const double *flux, double *out, hipStream_t s);
+// The boundary flux := *from (device memory), or v where from is null; the
+// partial sums and the other words of acc are cleared.
+hipError_t launch_set_flux(double *acc, double *flux, const double *from, double v, hipStream_t s);
 // p[0..n) := 0 (a kernel, so that no memset node lands in a captured graph).
 hipError_t launch_zero(double *p, int64_t n, hipStream_t s);
 // *p = v, and *p += k (one thread each; a kernel, not a memset, so that the
 // second can sit in a captured graph).
 hipError_t launch_set_time(int64_t *p, int64_t v, hipStream_t s);
 hipError_t launch_add_time(int64_t *p, int64_t k, hipStream_t s);
-// Sum of the stored deviations of buffer `src` into d.partial[0] (FP64).
+// Sum of the stored deviations of buffer `src` into d.partial[0] (FP64), the
+// boundary flux into d.acc[1].
 hipError_t launch_mass(const LaunchCfg &cfg, const Layout &L, const DevPtrs &d, int src,
                        hipStream_t s);
 

@@ -382,17 +382,18 @@ __global__ __launch_bounds__(kBlock) void k_mass_partial(const T *__restrict__ A
   }
 }
 
-__global__ __launch_bounds__(kBlock) void k_mass_final(double *partial, int64_t nparts) {
-  __shared__ double red[kBlock / 64];
+// partial[0] = the mass, acc[1] = the boundary flux.
+__global__ __launch_bounds__(kBlock) void k_mass_final(double *partial, int64_t nparts, double *acc,
+                                                       const double *flux) {
+  __shared__ double red[2][kBlock / 64];
+  const double share = flux_share(flux);
   double s = 0.0;
   for (int64_t k = threadIdx.x; k < nparts; k += kBlock) s += partial[1 + k];
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
+  const double m = block_sum(s, red[0]);
+  const double f = block_sum(share, red[1]);
   if (threadIdx.x == 0) {
-    double b = 0.0;
-    for (int w = 0; w < kBlock / 64; ++w) b += red[w];
-    partial[0] = b;
+    partial[0] = m;
+    acc[1] = acc[0] + f;
   }
 }
 
@@ -405,12 +406,16 @@ __global__ void k_windkessel(GatherArgs a) {
 __global__ void k_set_time(int64_t *p, int64_t v) { *p = v; }
 __global__ void k_add_time(int64_t *p, int64_t k) { *p += k; }
 
-__global__ __launch_bounds__(kBlock) void k_fold_flux(double *acc, double *flux) {
+__global__ __launch_bounds__(kBlock) void k_total_flux(const double *acc, const double *flux, double *out) {
   __shared__ double red[kBlock / 64];
-  const double s = sum_flux(flux, red);
-  if (threadIdx.x == 0) acc[0] += s;
-#pragma unroll
-  for (int k = threadIdx.x; k < kFluxSlots; k += kBlock) flux[k] = 0.0;
+  const double f = block_sum(flux_share(flux), red);
+  if (threadIdx.x == 0) *out = acc[0] + f;
+}
+
+__global__ __launch_bounds__(kBlock) void k_set_flux(double *acc, double *flux, const double *from, double v) {
+  const int k = blockIdx.x * kBlock + threadIdx.x;
+  flux[k] = 0.0;
+  if (k < 4) acc[k] = k == 0 ? (from ? *from : v) : 0.0;
 }
 
 __global__ void k_zero(double *p, int64_t n) {
@@ -570,7 +575,7 @@ hipError_t mass_impl(const Layout &L, const DevPtrs &d, int src, hipStream_t s) 
   int64_t nb = blocks_for(L.np);
   if (nb > d.partial_len - 1) nb = d.partial_len - 1;
   k_mass_partial<T><<<(unsigned)nb, kBlock, 0, s>>>(static_cast<const T *>(d.f[src]), d.order, L.np, d.partial);
-  k_mass_final<<<1, kBlock, 0, s>>>(d.partial, nb);
+  k_mass_final<<<1, kBlock, 0, s>>>(d.partial, nb, d.acc, d.flux);
   return hipGetLastError();
 }
 
@@ -624,8 +629,13 @@ hipError_t launch_add_time(int64_t *p, int64_t k, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_fold_flux(double *acc, double *flux, hipStream_t s) {
-  k_fold_flux<<<1, kBlock, 0, s>>>(acc, flux);
+hipError_t launch_total_flux(const double *acc, const double *flux, double *out, hipStream_t s) {
+  k_total_flux<<<1, kBlock, 0, s>>>(acc, flux, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_set_flux(double *acc, double *flux, const double *from, double v, hipStream_t s) {
+  k_set_flux<<<kFluxSlots / kBlock, kBlock, 0, s>>>(acc, flux, from, v);
   return hipGetLastError();
 }
 

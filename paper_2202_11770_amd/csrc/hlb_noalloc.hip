@@ -56,20 +56,17 @@ __global__ __launch_bounds__(kBlock) void k_mass_partial_na(const T *__restrict_
 __global__ __launch_bounds__(kBlock) void k_mass_balance_na(const double *partial, int64_t nparts, double offset,
                                                             double m0, const double *acc, const double *flux,
                                                             double *out) {
-  __shared__ double red[kBlock / 64];
-  double s = 0.0, M = 0.0;
+  __shared__ double red[2][kBlock / 64];
+  const double share = flux_share(flux);
+  double s = 0.0;
   for (int64_t k = threadIdx.x; k < nparts; k += kBlock) s += partial[1 + k];
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
+  const double b = block_sum(s, red[0]);
+  const double f = block_sum(share, red[1]);
   if (threadIdx.x == 0) {
-    double b = 0.0;
-    for (int w = 0; w < kBlock / 64; ++w) b += red[w];
-    M = offset + b;
+    const double M = offset + b;
     out[0] = M;
+    out[1] = M - m0 - (acc[0] + f);
   }
-  const double f = sum_flux(flux, red);
-  if (threadIdx.x == 0) out[1] = M - m0 - (acc[0] + f);
 }
 
 template <typename T>

@@ -401,8 +401,7 @@ hlb_status compute_mass(hlb_ctx *c, double *sum_g) {
 }
 
 hlb_status reset_balance(hlb_ctx *c) {
-  HIP_TRY(launch_zero(c->d.acc, 4, c->stream));
-  HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
+  HIP_TRY(launch_set_flux(c->d.acc, c->d.flux, nullptr, 0.0, c->stream));
   double s = 0;
   hlb_status st = compute_mass(c, &s);
   if (st) return st;
@@ -1461,9 +1460,8 @@ hlb_status hlb_mass_balance(hlb_ctx *c, double *mass, double *residual) {
   if (hlb_status st = check_ctx(c)) return st;
   if (hlb_status st = bind(c)) return st;
   double s = 0.0, flux = 0.0;
-  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
   if (hlb_status st = compute_mass(c, &s)) return st;
-  HIP_TRY(hipMemcpy(&flux, c->d.acc, sizeof(double), hipMemcpyDeviceToHost));
+  HIP_TRY(hipMemcpy(&flux, c->d.acc + 1, sizeof(double), hipMemcpyDeviceToHost));
   const double M = mass_offset(c) + s;
   if (mass) *mass = M;
   if (residual) *residual = M - c->m0 - flux;
@@ -1583,8 +1581,7 @@ hlb_status hlb_snapshot_save(hlb_ctx *c, int32_t slot) {
   auto &s = c->snaps[slot];
   HIP_TRY(hipMemcpyAsync(s.f[0], c->d.f[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(s.f[1], c->d.f[1], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
-  HIP_TRY(hipMemcpyAsync(s.acc, c->d.acc, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
+  HIP_TRY(launch_total_flux(c->d.acc, c->d.flux, s.acc, c->stream));
   s.t = c->t; s.t0 = c->t0; s.m0 = c->m0; s.cur = c->cur; s.direct = c->direct; s.valid = true;
   return HLB_OK;
 }
@@ -1597,8 +1594,7 @@ hlb_status hlb_snapshot_restore(hlb_ctx *c, int32_t slot) {
   if (hlb_status st = bind(c)) return st;
   HIP_TRY(hipMemcpyAsync(c->d.f[0], s.f[0], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.f[1], s.f[1], buf_bytes(c), hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->d.acc, s.acc, sizeof(double), hipMemcpyDeviceToDevice, c->stream));
-  HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
+  HIP_TRY(launch_set_flux(c->d.acc, c->d.flux, s.acc, 0.0, c->stream));
   c->t = s.t; c->t0 = s.t0; c->m0 = s.m0; c->cur = s.cur; c->direct = s.direct;
   return HLB_OK;
 }
@@ -1629,8 +1625,8 @@ hlb_status hlb_state_save(hlb_ctx *c, void *buf) {
   h.n_sites = c->L.n_sites; h.np = c->L.np; h.t = c->t; h.t0 = c->t0;
   h.storage = c->cfg.storage; h.cur = c->cur; h.direct = c->direct ? 1 : 0; h.m0 = c->m0;
   h.scheme = c->cfg.scheme;
-  HIP_TRY(launch_fold_flux(c->d.acc, c->d.flux, c->stream));
-  HIP_TRY(hipMemcpyAsync(h.acc, c->d.acc, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(launch_total_flux(c->d.acc, c->d.flux, c->d.acc + 1, c->stream));
+  HIP_TRY(hipMemcpyAsync(h.acc, c->d.acc + 1, sizeof(double), hipMemcpyDeviceToHost, c->stream));
   char *b = static_cast<char *>(buf);
   HIP_TRY(hipMemcpyAsync(b + sizeof(h), c->d.f[0], buf_bytes(c), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipMemcpyAsync(b + sizeof(h) + buf_bytes(c), c->d.f[1], buf_bytes(c), hipMemcpyDeviceToHost, c->stream));
@@ -1651,8 +1647,7 @@ hlb_status hlb_state_load(hlb_ctx *c, const void *buf) {
   const char *b = static_cast<const char *>(buf);
   HIP_TRY(hipMemcpyAsync(c->d.f[0], b + sizeof(h), buf_bytes(c), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipMemcpyAsync(c->d.f[1], b + sizeof(h) + buf_bytes(c), buf_bytes(c), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(hipMemcpyAsync(c->d.acc, h.acc, sizeof(double), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(launch_zero(c->d.flux, kFluxSlots, c->stream));
+  HIP_TRY(launch_set_flux(c->d.acc, c->d.flux, nullptr, h.acc[0], c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->t = h.t; c->t0 = h.t0; c->m0 = h.m0; c->cur = h.cur; c->direct = h.direct != 0;
   return HLB_OK;
