@@ -190,7 +190,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kAdjWave
     uint32_t walls = 0;  // bit i: the pull entry of direction i is a wall link
     if (bulk) {
       double g[Q];
-      gather<false, POROUS, false, NARROW, true>(A.S, p, blk, a, g, nullptr, lrow);
+      gather<POROUS, false, NARROW>(A.S, p, a, g, lrow);
       int32_t off[Q - 1];
       lds_offsets(lrow, off);
       if constexpr (NARROW) {

@@ -517,7 +517,8 @@ struct NextIolet {
 // iolet are then filled together from registers.  Per link, with a load of
 // code, source, record, value and coefficient one after the other, the step
 // of the 203,352-site tree with Windkessel outlets took 33 us in FP64 and 29
-// in FP32; so it takes 20.6 and 14.8 us (event time).
+// in FP32; so it takes 20.6 and 14.8 us (event time).  With a.io_flux set the
+// outflow of Windkessel outlets goes to *wkf (which must then be given).
 // Its registers decide its speed: within the 80 (FP32, FP16) or 128 (FP64) of
 // the step kernel it has to run without scratch memory.  The barriers for the
 // scheduler, the coefficients in two batches and the addresses formed where
@@ -615,28 +616,22 @@ __device__ inline C gather_iolet(const T *__restrict__ A, int64_t p, const Gathe
 //                                 m = x - c_i/2, U = A_k(t) W(m) v_k
 //   pressure iolet (ghost rho):   f_i = f_i^eq(rho_k(t), (u.n) n),
 //                                 u the site's velocity at time t
-// Returns the mass the boundary rules added (filled - reflected).  With
-// a.io_flux set, the outflow of Windkessel outlets goes to *wkf (which must
-// then be given).
-// IOLET = false: the site has only fluid and wall links.
-// blk: the kSegBlock-position block of p (bulk+wall group only).
+// gather_iolet() takes the sites of the iolet groups, gather() those of the
+// bulk+wall group, which have fluid and wall links alone: every link,
+// bounce-back included, is one load, and the offsets (p's segment row, staged
+// in LDS at lrow) are fetched before the 18 gathers are issued.
+// Returns the mass the boundary rules added (filled - reflected).
 // NARROW: see at().
-// LROWS (bulk+wall group): p's segment row is staged in LDS at lrow (see
-// lds_offsets).
-template <bool IOLET, bool POROUS, bool SH, bool NARROW = false, bool LROWS = false, typename T, typename C>
-__device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, const GatherArgs &a, C (&g)[Q],
-                           WkFlux *wkf = nullptr, const int4 *lrow = nullptr) {
+template <bool POROUS, bool SH, bool NARROW, typename T, typename C>
+__device__ inline C gather(const T *__restrict__ A, int64_t p, const GatherArgs &a, C (&g)[Q], const int4 *lrow) {
   const int64_t np = a.np;
-  C flux = 0;
-  if constexpr (!IOLET && NARROW) {
-    // Bulk+wall group, buffers of at most 4 GiB (see Narrow).  A wall link's
-    // offset np puts jb at or above sz np + D.
+  int32_t off[Q - 1];
+  lds_offsets(lrow, off);
+  uint32_t walls = 0;
+  if constexpr (NARROW) {
+    // Buffers of at most 4 GiB (see Narrow).  A wall link's offset np puts jb
+    // at or above sz np + D.
     using N = Narrow<T>;
-    int32_t off[Q - 1];
-    if constexpr (LROWS)
-      lds_offsets(lrow, off);
-    else
-      bulk_offsets(a, p, blk, off);
     // The empty asm statements keep pb whole (so that each jb is one
     // shift-and-add) and make every lane compute its neighbour's offset (so
     // that the wall choice stays a select instead of a branch).
@@ -645,7 +640,6 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
     const uint32_t own = N::voff(pb);
     const uint32_t wall_lo = own - N::D, wall_hi = own + N::D;  // (p, opp(i)) for even / odd i
     const uint32_t jb_wall = ((uint32_t)np << N::S) + N::D;
-    uint32_t walls = 0;
     g[0] = ld(N::at(A, 0, own));
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
@@ -656,17 +650,8 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
       g[i] = ld(N::at(A, i, wall ? (opp(i) > i ? wall_hi : wall_lo) : vj));
       if constexpr (POROUS) walls |= (uint32_t)wall << i;
     }
-    if constexpr (POROUS) flux = porous_walls<SH>(a, p, walls, g);
-  } else if constexpr (!IOLET) {
-    // Bulk+wall group: every link, bounce-back included, is one load; the
-    // offsets are fetched before the 18 gathers are issued.
-    int32_t off[Q - 1];
-    if constexpr (LROWS)
-      lds_offsets(lrow, off);
-    else
-      bulk_offsets(a, p, blk, off);
+  } else {
     const int32_t p32 = (int32_t)p;
-    uint32_t walls = 0;
     g[0] = ld(at<NARROW>(A, p32, 0));
 #pragma unroll
     for (int i = 1; i < Q; ++i) {
@@ -677,14 +662,12 @@ __device__ inline C gather(const T *__restrict__ A, int64_t p, int64_t blk, cons
       g[i] = ld(at<NARROW>(A, wall ? p32 : j, wall ? opp(i) : i));
       if constexpr (POROUS) walls |= (uint32_t)wall << i;
     }
-    if constexpr (POROUS) flux = porous_walls<SH>(a, p, walls, g);
-  } else {
-    flux = gather_iolet<POROUS, SH, NARROW>(A, p, a, g, wkf);
   }
-  return flux;
+  if constexpr (POROUS) return porous_walls<SH>(a, p, walls, g);
+  return C(0);
 }
 
-// Two bulk+wall sites at once (gather<false, ...> for p and p2): both offset
+// Two bulk+wall sites at once (gather() for p and p2): both offset
 // rows are fetched, then all 38 population loads are issued before any is
 // used (the scheduling barrier keeps the compiler from interleaving the two
 // sites' loads with the first site's arithmetic), so that a wavefront has

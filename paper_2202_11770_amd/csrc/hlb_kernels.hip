@@ -51,7 +51,7 @@ using namespace dev;
 // The push step's iolet path keeps more values at once: FP16 takes 6 waves
 // there (28 to 36 bytes of scratch; with 7, 68 to 84, and 10 steps of the
 // 13,312-site pipe take 85.6 us instead of 77.5, of the 1.1e6-site tree 306 instead of 296).
-template <typename T, int SPT = 1, bool NARROW = true>
+template <typename T, int SPT = 1>
 constexpr int kStepWaves = SPT == 2 ? 4 : (std::is_same<T, double>::value ? 4 : sizeof(T) == 2 ? 7 : 6);
 template <typename T>
 constexpr int kPushWaves = std::is_same<T, double>::value ? 4 : 6;
@@ -70,7 +70,7 @@ constexpr bool kStepShortRows = sizeof(T) == 2;
 // before either collides, which doubles the bytes a wavefront has in flight.
 // nb_bulk then counts block pairs.  Only the full step (blk0 = 0) uses it.
 template <typename T, bool POROUS, bool NARROW, bool CACHED, int SPT = 1>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T, SPT, NARROW>, 8))) void k_step(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWaves<T, SPT>, 8))) void k_step(
     const T *__restrict__ A, T *__restrict__ B, GatherArgs a, const int32_t *__restrict__ order, int64_t n0,
     int64_t nb_io, int64_t blk0, int64_t nb_bulk, int xcd_chunk, typename Acc<T>::type omega, double *flux_slots,
     uint32_t *done) {
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kStepWav
     const int4 *lrow = stage_rows<kStepShortRows<T> || CACHED>(a, blk, p, n0, lrows);
     if (p < n0) {
       C g[Q];
-      flux = gather<false, POROUS, SH, NARROW, true>(A, p, blk, a, g, nullptr, lrow);
+      flux = gather<POROUS, SH, NARROW>(A, p, a, g, lrow);
       collide<SH>(g, omega, C(a.rho0));
       if constexpr (NARROW) {
         using N = Narrow<T>;
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
 #pragma unroll
     for (int i = 0; i < Q; ++i) g[i] = ld(at<NARROW>(A, p32, i));
   } else if (bulk) {
-    gather<false, POROUS, SH, NARROW, true>(A, p, blk, a, g, nullptr, lrow);
+    gather<POROUS, SH, NARROW>(A, p, a, g, lrow);
   } else {
     gather_iolet<POROUS, SH, NARROW>(A, p, a, g, nullptr);
   }
