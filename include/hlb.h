@@ -145,10 +145,17 @@ typedef struct {
                           graphs as fit and launches the rest one by one;
                           0 (default): every step is its own launch.  A
                           graph is recaptured when a buffer, table pointer,
-                          porosity or Windkessel setting changes; it is not
-                          used while timing is on.  Results do not depend on
-                          it (bit for bit, except where atomics already make
-                          the Windkessel outflow order-dependent). */
+                          porosity or Windkessel setting changes; the first
+                          replay and the first after a change wait for the
+                          stream.  It is not used while timing is on.
+                          Results do not depend on it (bit for bit, except
+                          where atomics already make the Windkessel outflow
+                          order-dependent).  It pays where launches bind:
+                          work of the null stream between calls puts a
+                          barrier of about 6 us before every launch on the
+                          context's own stream, and several small
+                          simulations at once wait for the host (4 us a
+                          launch). */
   int32_t order_block; /* log2 of the band / column width of
                           HLB_ORDER_BANDS and HLB_ORDER_COLUMNS, 1..16
                           (default 7); ignored by the other orders */
@@ -328,8 +335,8 @@ hlb_status hlb_stats(hlb_ctx *ctx, hlb_stats_t *stats);
  *   rho_k(s+1) = rho_ref + R1 Q_k(s) + X(s+1),
  *   X(s+1) = X(s) + (Q_k(s) - X(s)/R2) / C   if C > 0 (no leak term if R2 = 0),
  *   X(s+1) = R2 Q_k(s)                       if C = 0 (resistance R1 + R2).
- * Each update's outflow is accumulated in FP64 by the step kernel and the
- * state advanced by one small kernel after it.  rho_k starts at rho_ref + X0.
+ * Each update's outflow is accumulated in FP64 by the step kernel, whose last
+ * block of iolet sites then advances the state.  rho_k starts at rho_ref + X0.
  * w = NULL turns the model off (the iolet keeps its last table);
  * hlb_set_iolet_table on the iolet also turns it off.  R1, C, R2 >= 0 and,
  * if C > 0 and R2 > 0, R2 C >= 1.  Not on a partition.  hlb_adjoint_run

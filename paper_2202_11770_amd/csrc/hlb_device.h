@@ -363,9 +363,9 @@ __device__ inline void bulk_offsets(const GatherArgs &a, int64_t p, int64_t blk,
 // SHORT: the rows' extent comes from two blocks' first segments, one scalar
 // load, with p's row index fetched beside it; else from the last position's
 // index, behind p's.  The short chain of loads takes FP16, whose blocks are the
-// shortest, from 140.2 to 138.3 us on the 7.8e6-site tree (against its rows
-// loaded per wavefront), and FP64 and FP32 while the state stays in the Infinity
-// Cache from 23.4 to 22.6 and 15.5 to 14.6 us (414,834 sites); from HBM those run 0.4%
+// shortest, from 140.2 to 136.9 us on the 7.8e6-site tree (against its rows
+// loaded per wavefront at 6 waves; at 7 waves with it), and FP64 and FP32 while
+// the state stays in the Infinity Cache from 23.4 to 22.6 and 15.5 to 14.6 us (414,834 sites); from HBM those run 0.4%
 // and 1.3% slower with it (2.0e7-site tree, 1036 to 1040 us, 554 to 562).  The
 // adjoint's step takes it too (2.95e6-site tree, 286 to 279 us inside the objective
 // window, 262 to 261 outside).
@@ -519,8 +519,9 @@ struct NextIolet {
 // of the 203,352-site tree with Windkessel outlets took 33 us in FP64 and 29
 // in FP32; so it takes 20.6 and 14.8 us (event time).  With a.io_flux set the
 // outflow of Windkessel outlets goes to *wkf (which must then be given).
-// Its registers decide its speed: within the 80 (FP32, FP16) or 128 (FP64) of
-// the step kernel it has to run without scratch memory.  The barriers for the
+// Its registers decide its speed: it fits the 80 (FP32) or 128 (FP64) of the
+// step kernel without scratch memory, and the 72 of FP16 with 20 bytes of it
+// (the seventh wave gains the bulk path more).  The barriers for the
 // scheduler, the coefficients in two batches and the addresses formed where
 // they are used see to that (with 56-140 bytes of scratch the FP32 step of the
 // 125,400-site vessel took 13.0 us instead of 8.7, with all coefficients in one

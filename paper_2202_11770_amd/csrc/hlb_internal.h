@@ -127,7 +127,10 @@ struct LaunchCfg {
 // 10.2 us at 32 MB for both buffers, 17.6 to 14.2 at 62, 35.2 to 31.7 at 182, 46.6 to 46.4
 // at 251, 55.5 to 59.6 at 305; FP32 11.6 to 9.8 at 31, 37.3 to 35.5 at 182, 42.9 to 41.3 at
 // 217, 50.7 to 53.1 at 269; FP16 10.2 to 9.4 at 23, 38.3 to 37.7 at 172, 50.3 to 54.7 at 231.
-// Below 20 MB neither is faster (FP16 at 11-15 MB: 7.6 to 8.0 us).
+// Below 20 MB cached stores gain nothing or lose (FP64 7.01 to 7.84 at 17.5, FP32 6.78 to
+// 6.71 at 14, 6.60 to 6.89 at 17, 6.57 to 6.95 at 19, FP16 6.78 to 6.91 at 13, 7.50 to 7.53 at 17), from
+// there on they gain in every storage (FP64 7.90 to 7.48 at 21, 8.97 to 8.32 at 27, FP32 7.37 to
+// 7.09 at 22, 8.40 to 7.72 at 26, FP16 10.2 to 8.95 at 25; pipes, vessels and trees).
 constexpr double kCacheMB = 208.0, kCacheFromMB = 20.0;
 inline double buffers_mb(int64_t np, size_t storage_bytes) { return 2e-6 * 19.0 * (double)np * (double)storage_bytes; }
 inline bool in_cache(int64_t np, size_t storage_bytes) {

@@ -252,9 +252,9 @@ __global__ __launch_bounds__(kBlock) void k_set_state(T *__restrict__ Pre, T *__
 // and addresses are the step kernel's (iolet groups first, XCD chunks,
 // segment rows in LDS, 32-bit offsets where a buffer allows), and the stress
 // is formed from six moments, only where a wavefront has wall sites, so that
-// the kernel runs at 4 waves per SIMD instead of 2: 862 -> 824 us on the 2.0e7-site
-// tree in FP64, 722 -> 556 in FP32, 282 -> 199 on the 7.8e6-site tree in FP16, 8.4 ->
-// 6.7 on the 13,312-site pipe (5 waves spill: 917 us).
+// the kernel runs at 4 waves per SIMD instead of 2: 863 -> 792 us on the 2.0e7-site
+// tree in FP64, 619 -> 528 in FP32, 250 -> 185 on the 7.8e6-site tree in FP16, 10.2 ->
+// 5.5 on the 13,312-site pipe, calls back to back (5 waves spill: 917 us in FP64).
 // SRC: whether A holds pre-collision values, read as they are, or the
 // post-collision values that they are gathered from.
 enum MacroSrc { kDirect, kPulled, kPulledPorous };
